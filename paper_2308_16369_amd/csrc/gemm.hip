@@ -17,6 +17,7 @@
 #include "kernels.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace sarathi {
 
@@ -330,10 +331,22 @@ __device__ __forceinline__ void rope_kv_epilogue(const GemmP& p, floatx4 (&acc)[
   }
 }
 
-template <int BM, int BN, int WGM, int WGN, int NP, int S, int EPI>
+//
+// fp32 (T = float): the same tiles of 128-byte k-rows (32 floats), products on
+// v_mfma_f32_16x16x4_f32 (full fp32 inputs and sums).  A lane's 16-byte chunk
+// holds four consecutive k of its row; product j of a chunk takes element j
+// of every lane, so each 16x16x4 product sums k = {j, 4 + j, 8 + j, 12 + j} of
+// a 16-wide step for both operands alike.  K need only be a multiple of 4:
+// the last k-tile's chunks past K are read from the row's last chunk and
+// zeroed in registers.  Bound by the fp32 matrix rate (157 TFLOP/s), 8x the
+// time per operand byte of bf16.
+template <typename T, int BM, int BN, int WGM, int WGN, int NP, int S, int EPI>
 __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p) {
   constexpr int NC = WGM * WGN;
-  constexpr int BK = 64;
+  constexpr int ES = sizeof(T);
+  constexpr int BK = 128 / ES;
+  constexpr bool F32 = ES == 4;
+  static_assert(!F32 || EPI != EPI_ROPE_KV, "the RoPE epilogue is bf16");
   constexpr int WTM = BM / WGM, WTN = BN / WGN;
   constexpr int FM = WTM / 16, FN = WTN / 16;
   constexpr int ROWS = BM + BN;
@@ -358,7 +371,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
   const int n0_out = tile_n * (EPI == EPI_SWIGLU ? BN / 2 : BN);
   const int kbeg = split * p.k_split;
   const int kend = min(p.K, kbeg + p.k_split);
-  const int nk = (kend - kbeg) / BK;
+  const int nk = (kend - kbeg + BK - 1) / BK;    // bf16: whole k-tiles; fp32: the last may be short
 
   if (wave >= NC) {
     // ---------------- producer
@@ -367,8 +380,8 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
     // group, so a request costs no vector instruction (global_load_lds with
     // a scalar base; the launcher keeps both matrices below 4 GiB).
     const int q = __builtin_amdgcn_readfirstlane(wave - NC);
-    const char* A = reinterpret_cast<const char*>(p.A) + (size_t)kbeg * 2;
-    const char* W = reinterpret_cast<const char*>(p.W) + (size_t)kbeg * 2;
+    const char* A = reinterpret_cast<const char*>(p.A) + (size_t)kbeg * ES;
+    const char* W = reinterpret_cast<const char*>(p.W) + (size_t)kbeg * ES;
     const int lchunk = (lane & 7) ^ (lane >> 3);
     uint32_t off[IHI];
 #pragma unroll
@@ -379,7 +392,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
       const size_t r = g < GA                  ? (size_t)min(m0 + row, p.M - 1)
                        : EPI == EPI_ROPE_KV ? (size_t)rope_w_row(n0_out + nl, p.N, p.rope.hd)
                                             : (size_t)w_row_of<EPI, WTN>(nl, n0_out, p.N);
-      off[j] = (uint32_t)(r * p.K * 2 + lchunk * 16);
+      off[j] = (uint32_t)(r * p.K * ES + lchunk * 16);
     }
     const bool extra = q < RHI;
     // With rotate_k, the G = tiles_m blocks that share a W panel take each
@@ -394,11 +407,15 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
         if (base + GR <= nk) kt = base + (kt - base + tile_m * RD) % GR;
       }
       uint4* dst = lds + stage * ROWS * 8;
-      const char* a_k = A + (size_t)kt * BK * 2;
-      const char* w_k = W + (size_t)kt * BK * 2;
+      const char* a_k = A + (size_t)kt * BK * ES;
+      const char* w_k = W + (size_t)kt * BK * ES;
+      // fp32: a short last k-tile's lanes past K re-read their row's last chunk
+      const uint32_t back =
+          F32 && kbeg + (kt + 1) * BK > kend ? 16u * max(lchunk - ((kend - kbeg - kt * BK) / 4 - 1), 0) : 0u;
 #pragma unroll
       for (int j = IHI - 1; j >= 0; --j)
-        if (j < ILO || extra) dma16((min(j * NP + q, ROWS / 8 - 1) < GA ? a_k : w_k) + off[j], dst + (j * NP + q) * 64);
+        if (j < ILO || extra)
+          dma16((min(j * NP + q, ROWS / 8 - 1) < GA ? a_k : w_k) + off[j] - back, dst + (j * NP + q) * 64);
     };
     auto wait_next = [&](bool all) {   // all but the newest S - 2 stages landed
       if (all) wait_vmcnt<0>();
@@ -437,22 +454,39 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
       const int ch = ks * 4 + (lane >> 4);
-      bf16x8_t af[FM], bfr[FN];
+      using Frag = std::conditional_t<F32, floatx4, bf16x8_t>;
+      Frag af[FM], bfr[FN];
 #pragma unroll
       for (int fm = 0; fm < FM; ++fm) {
         const int r = wm * WTM + fm * 16 + (lane & 15);
-        af[fm] = __builtin_bit_cast(bf16x8_t, s[r * 8 + (ch ^ (r & 7))]);
+        af[fm] = __builtin_bit_cast(Frag, s[r * 8 + (ch ^ (r & 7))]);
       }
 #pragma unroll
       for (int fn = 0; fn < FN; ++fn) {
         const int r = BM + wn * WTN + fn * 16 + (lane & 15);
-        bfr[fn] = __builtin_bit_cast(bf16x8_t, s[r * 8 + (ch ^ (r & 7))]);
+        bfr[fn] = __builtin_bit_cast(Frag, s[r * 8 + (ch ^ (r & 7))]);
       }
+      if constexpr (F32) {
+        if (kbeg + (kt + 1) * BK > kend && kbeg + kt * BK + ch * 4 >= kend) {   // chunks past K: both operands zero
 #pragma unroll
-      for (int fm = 0; fm < FM; ++fm)
+          for (int fm = 0; fm < FM; ++fm) af[fm] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int fn = 0; fn < FN; ++fn)
-          acc[fm][fn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[fm], bfr[fn], acc[fm][fn], 0, 0, 0);
+          for (int fn = 0; fn < FN; ++fn) bfr[fn] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+            for (int fn = 0; fn < FN; ++fn)
+              acc[fm][fn] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[fm][j], bfr[fn][j], acc[fm][fn], 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+          for (int fn = 0; fn < FN; ++fn)
+            acc[fm][fn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[fm], bfr[fn], acc[fm][fn], 0, 0, 0);
+      }
     }
     lds_read_barrier();
     buf = (buf + 1 == S) ? 0 : buf + 1;
@@ -474,14 +508,14 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
           const int c = n0_out + wn * (WTN / 2) + fn * 16 + (lane & 15);
           if (c < p.N) {
             const float v = silu_f(acc[fm][fn][i]) * acc[fm][fn + FN / 2][i];
-            reinterpret_cast<bf16*>(p.out)[(size_t)r * p.N + c] = f2bf(v);
+            reinterpret_cast<T*>(p.out)[(size_t)r * p.N + c] = from_f<T>(v);
           }
         }
       } else {
 #pragma unroll
         for (int fn = 0; fn < FN; ++fn) {
           const int c = n0_out + wn * WTN + fn * 16 + (lane & 15);
-          if (c < p.N) epi_store<bf16, EPI>(p, r, c, acc[fm][fn][i], split);
+          if (c < p.N) epi_store<T, EPI>(p, r, c, acc[fm][fn][i], split);
         }
       }
     }
@@ -596,14 +630,14 @@ static hipError_t run_bf16(GemmP p, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WGM, int WGN, int NP, int S, int EPI>
-static hipError_t run_ws(GemmP p, hipStream_t s) {
+template <typename T, int BM, int BN, int WGM, int WGN, int NP, int S, int EPI>
+static hipError_t run_ws(const GemmP& p, hipStream_t s) {
   const size_t lds_bytes = (size_t)S * (BM + BN) * 8 * sizeof(uint4);
   static std::atomic<uint64_t> lds_set{0};   // devices on which this instance's LDS limit is raised
-  hipError_t e = ensure_dynamic_lds((const void*)gemm_ws_kernel<BM, BN, WGM, WGN, NP, S, EPI>, (int)lds_bytes, lds_set);
+  hipError_t e = ensure_dynamic_lds((const void*)gemm_ws_kernel<T, BM, BN, WGM, WGN, NP, S, EPI>, (int)lds_bytes, lds_set);
   if (e != hipSuccess) return e;
   const int grid = (p.n_tiles + 7) / 8 * 8;
-  hipLaunchKernelGGL((gemm_ws_kernel<BM, BN, WGM, WGN, NP, S, EPI>), dim3(grid), dim3(64 * (WGM * WGN + NP)),
+  hipLaunchKernelGGL((gemm_ws_kernel<T, BM, BN, WGM, WGN, NP, S, EPI>), dim3(grid), dim3(64 * (WGM * WGN + NP)),
                      lds_bytes, s, p);
   return hipGetLastError();
 }
@@ -668,16 +702,16 @@ constexpr int kNumWsTiles = sizeof(kWsTiles) / sizeof(kWsTiles[0]);
 template <int EPI>
 static hipError_t run_ws_cfg(int cfg, const GemmP& p, hipStream_t s) {
   switch (cfg) {
-    case 0: return run_ws<64, 64, 2, 2, 4, 6, EPI>(p, s);
-    case 1: return run_ws<64, 128, 2, 4, 4, 6, EPI>(p, s);
-    case 2: return run_ws<64, 256, 2, 4, 4, 3, EPI>(p, s);
-    case 3: return run_ws<96, 128, 2, 4, 4, 5, EPI>(p, s);
-    case 4: return run_ws<96, 192, 2, 6, 4, 4, EPI>(p, s);
-    case 5: return run_ws<96, 256, 2, 4, 4, 3, EPI>(p, s);
-    case 6: return run_ws<160, 128, 2, 4, 4, 4, EPI>(p, s);
-    case 7: return run_ws<160, 192, 2, 6, 4, 3, EPI>(p, s);
-    case 8: return run_ws<160, 224, 2, 7, 2, 3, EPI>(p, s);
-    default: return run_ws<160, 256, 2, 4, 4, 3, EPI>(p, s);
+    case 0: return run_ws<bf16, 64, 64, 2, 2, 4, 6, EPI>(p, s);
+    case 1: return run_ws<bf16, 64, 128, 2, 4, 4, 6, EPI>(p, s);
+    case 2: return run_ws<bf16, 64, 256, 2, 4, 4, 3, EPI>(p, s);
+    case 3: return run_ws<bf16, 96, 128, 2, 4, 4, 5, EPI>(p, s);
+    case 4: return run_ws<bf16, 96, 192, 2, 6, 4, 4, EPI>(p, s);
+    case 5: return run_ws<bf16, 96, 256, 2, 4, 4, 3, EPI>(p, s);
+    case 6: return run_ws<bf16, 160, 128, 2, 4, 4, 4, EPI>(p, s);
+    case 7: return run_ws<bf16, 160, 192, 2, 6, 4, 3, EPI>(p, s);
+    case 8: return run_ws<bf16, 160, 224, 2, 7, 2, 3, EPI>(p, s);
+    default: return run_ws<bf16, 160, 256, 2, 4, 4, 3, EPI>(p, s);
   }
 }
 
@@ -690,6 +724,36 @@ static hipError_t run_ws_epi(int epi, int cfg, const GemmP& p, hipStream_t s) {
     case EPI_RESIDF32_TO_ACT: return run_ws_cfg<EPI_RESIDF32_TO_ACT>(cfg, p, s);
     case EPI_ROPE_KV: return run_ws_cfg<EPI_ROPE_KV>(cfg, p, s);
     default: return run_ws_cfg<EPI_PARTIAL>(cfg, p, s);
+  }
+}
+
+// fp32 tiles of the same kernel (4 consumer waves of 2 x 2, or 8 of 2 x 4; the
+// 32-row ones 2 x 1 and 2 x 2), and their ring depth (48-112 KB; the 32-row
+// tiles leave room for two or three blocks per CU).
+constexpr WsTile kF32Tiles[] = {{32, 32}, {32, 64}, {64, 64}, {96, 64}, {160, 64}, {96, 128}, {160, 128}};
+constexpr int kNumF32Tiles = sizeof(kF32Tiles) / sizeof(kF32Tiles[0]);
+
+template <int EPI>
+static hipError_t run_ws_f32_cfg(int cfg, const GemmP& p, hipStream_t s) {
+  switch (cfg) {
+    case 0: return run_ws<float, 32, 32, 2, 1, 2, 6, EPI>(p, s);
+    case 1: return run_ws<float, 32, 64, 2, 2, 2, 6, EPI>(p, s);
+    case 2: return run_ws<float, 64, 64, 2, 2, 4, 6, EPI>(p, s);
+    case 3: return run_ws<float, 96, 64, 2, 2, 4, 5, EPI>(p, s);
+    case 4: return run_ws<float, 160, 64, 2, 2, 4, 4, EPI>(p, s);
+    case 5: return run_ws<float, 96, 128, 2, 4, 4, 4, EPI>(p, s);
+    default: return run_ws<float, 160, 128, 2, 4, 4, 3, EPI>(p, s);
+  }
+}
+
+static hipError_t run_ws_f32(int epi, int cfg, const GemmP& p, hipStream_t s) {
+  switch (epi) {
+    case EPI_STORE: return run_ws_f32_cfg<EPI_STORE>(cfg, p, s);
+    case EPI_GELU: return run_ws_f32_cfg<EPI_GELU>(cfg, p, s);
+    case EPI_SWIGLU: return run_ws_f32_cfg<EPI_SWIGLU>(cfg, p, s);
+    case EPI_RESID_TO_F32: return run_ws_f32_cfg<EPI_RESID_TO_F32>(cfg, p, s);
+    case EPI_RESIDF32_TO_ACT: return run_ws_f32_cfg<EPI_RESIDF32_TO_ACT>(cfg, p, s);
+    default: return run_ws_f32_cfg<EPI_PARTIAL>(cfg, p, s);
   }
 }
 
@@ -731,6 +795,32 @@ static WsChoice pick_ws(int M, int N, int K, bool swiglu, int max_split) {
   return best;
 }
 
+// The same for fp32: a 32-wide k-tile costs its products at the fp32 matrix
+// rate (256 flop per clock and CU) or its operand feed, whichever is longer,
+// and at least a barrier round trip; small shapes are bound by the fill and
+// the number of k-tiles in a row, so they take many small tiles.
+static WsChoice pick_f32(int M, int N, int K, bool swiglu, int max_split) {
+  WsChoice best{0, 1};
+  double best_t = 1e300;
+  for (int c = 0; c < kNumF32Tiles; ++c) {
+    const int bm = kF32Tiles[c].bm, bn = kF32Tiles[c].bn;
+    const int per = swiglu ? bn / 2 : bn;
+    const long tiles = (long)((M + bm - 1) / bm) * ((N + per - 1) / per);
+    const double per_k = std::max(std::max(1.04e-4 * bm * bn * 1.1, 1.9e-3 * bm + 4.2e-3 * bn), 0.15);   // us
+    for (int ns = 1; ns <= max_split; ++ns) {
+      const double rounds = (double)((tiles * ns + 255) / 256);
+      const double k_tiles = 4.0 * (((K + 127) / 128 + ns - 1) / ns);        // whole groups of four per split
+      double t = rounds * (k_tiles * per_k + 2.0 + (double)bm * per * 4.0 / 4.0e4);
+      if (ns > 1) t += (ns + 2) * 4.0 * (double)M * N / 5.5e6 + 3.0;
+      if (t < best_t * 0.999) {
+        best_t = t;
+        best = {c, ns};
+      }
+    }
+  }
+  return best;
+}
+
 int linear_tile_count() { return kNumWsTiles; }
 bool linear_tile_shape(int tile, int* bm, int* bn) {
   if (tile < 0 || tile >= kNumWsTiles) return false;
@@ -749,40 +839,65 @@ hipError_t launch_linear(int dtype, const LinearArgs& a, hipStream_t s, int forc
   p.k_split = a.K; p.n_split = 1;
 
   if (dtype == 0) {
-    // Split-K for the residual ops when the 64x64 tiles leave most CUs idle:
-    // fp32 partials per split of whole 64-wide k-steps, then residual +
-    // partials added in split order (deterministic).
     const bool resid_kind = a.kind == LIN_RESID || a.kind == LIN_RESID_F32IN;
-    const int tiles = ((a.M + 63) / 64) * ((a.N + 63) / 64);
-    if (resid_kind && a.parts != nullptr && tiles < 64) {
-      int ns = std::min(std::min(MAX_SPLIT, (64 + tiles - 1) / tiles), (a.K + 127) / 128);
-      ns = (int)std::min<size_t>((size_t)ns, a.parts_cap / ((size_t)a.M * a.N));
-      if (ns > 1) {
-        const int steps = (a.K + 63) / 64;
-        p.k_split = (steps + ns - 1) / ns * 64;
-        p.n_split = (a.K + p.k_split - 1) / p.k_split;
-        p.out = a.parts;
-        if (plan) {
-          *plan = LinearPlan{64, 64, p.n_split};
-          return hipSuccess;
-        }
-        hipError_t e = run_f32<EPI_PARTIAL>(p, s);
-        if (e != hipSuccess) return e;
-        return launch_split_reduce(0, a.kind == LIN_RESID_F32IN, a.kind == LIN_RESID, a.resid, a.parts, p.n_split,
-                                   (size_t)a.M * a.N, a.out, s);
-      }
+    const bool swiglu = a.kind == LIN_SWIGLU;
+    // Split-K of the residual ops: fp32 partials per split of whole groups of
+    // four 32-wide k-tiles, then residual + partials added in split order
+    // (deterministic).
+    int max_split = 1;
+    if (resid_kind && a.parts != nullptr) {
+      max_split = std::min(MAX_SPLIT, (a.K + 127) / 128);
+      max_split = (int)std::min<size_t>((size_t)max_split, a.parts_cap / ((size_t)a.M * a.N));
+      max_split = std::max(max_split, 1);
+    }
+    // matrix-core kernel: x and W each under 4 GiB (32-bit row offsets);
+    // sizes past that take the register-staged vector kernel
+    const size_t w_rows = swiglu ? 2 * (size_t)a.N : (size_t)a.N;
+    const bool ws = (size_t)a.M * a.K * 4 < (1ull << 32) && w_rows * a.K * 4 < (1ull << 32);
+    WsChoice ch{2, 1};
+    if (ws) {
+      ch = pick_f32(a.M, a.N, a.K, swiglu, max_split);
+    } else {
+      const int tiles = ((a.M + 63) / 64) * ((a.N + 63) / 64);
+      if (tiles < 64) ch.n_split = std::min(max_split, (64 + tiles - 1) / tiles);
+    }
+    const int bm = ws ? kF32Tiles[ch.cfg].bm : 64, bn = ws ? kF32Tiles[ch.cfg].bn : 64;
+    const int groups = (a.K + 127) / 128;
+    if (ch.n_split > 1) {
+      p.k_split = (groups + ch.n_split - 1) / ch.n_split * 128;
+      p.n_split = (a.K + p.k_split - 1) / p.k_split;
     }
     if (plan) {
-      *plan = LinearPlan{64, 64, 1};
+      *plan = LinearPlan{bm, bn, p.n_split};
       return hipSuccess;
     }
-    switch (a.kind) {
-      case LIN_PLAIN: return run_f32<EPI_STORE>(p, s);
-      case LIN_GELU: return run_f32<EPI_GELU>(p, s);
-      case LIN_SWIGLU: return run_f32<EPI_SWIGLU>(p, s);
-      case LIN_RESID: return run_f32<EPI_RESID_TO_F32>(p, s);
-      default: return run_f32<EPI_RESIDF32_TO_ACT>(p, s);
+    const bool split = p.n_split > 1;
+    if (split) p.out = a.parts;
+    const int epi = split                      ? EPI_PARTIAL
+                    : a.kind == LIN_PLAIN      ? EPI_STORE
+                    : a.kind == LIN_GELU       ? EPI_GELU
+                    : a.kind == LIN_SWIGLU     ? EPI_SWIGLU
+                    : a.kind == LIN_RESID      ? EPI_RESID_TO_F32
+                                               : EPI_RESIDF32_TO_ACT;
+    hipError_t e;
+    if (ws) {
+      p.tiles_m = (a.M + bm - 1) / bm;
+      p.tiles_n = (a.N + (swiglu ? bn / 2 : bn) - 1) / (swiglu ? bn / 2 : bn);
+      p.n_tiles = p.tiles_m * p.tiles_n * p.n_split;
+      e = run_ws_f32(epi, ch.cfg, p, s);
+    } else {
+      switch (epi) {
+        case EPI_STORE: e = run_f32<EPI_STORE>(p, s); break;
+        case EPI_GELU: e = run_f32<EPI_GELU>(p, s); break;
+        case EPI_SWIGLU: e = run_f32<EPI_SWIGLU>(p, s); break;
+        case EPI_RESID_TO_F32: e = run_f32<EPI_RESID_TO_F32>(p, s); break;
+        case EPI_RESIDF32_TO_ACT: e = run_f32<EPI_RESIDF32_TO_ACT>(p, s); break;
+        default: e = run_f32<EPI_PARTIAL>(p, s); break;
+      }
     }
+    if (e != hipSuccess || !split) return e;
+    return launch_split_reduce(0, a.kind == LIN_RESID_F32IN, a.kind == LIN_RESID, a.resid, a.parts, p.n_split,
+                               (size_t)a.M * a.N, a.out, s);
   }
 
   int epi;
