@@ -34,6 +34,7 @@ struct GemmP {
                         // rotate their k-tile order
   void* out;            // [M, N]: dtype, or fp32 for EPI_RESID_TO_F32; EPI_PARTIAL: fp32 [n_split][M, N]
   const void* resid;    // EPI_RESID_TO_F32: dtype [M,N]; EPI_RESIDF32_TO_ACT: fp32 [M,N]
+  int vec4;             // N a multiple of 4 and out / resid 16-byte aligned: four columns per store
   RopeArgs rope;        // EPI_ROPE_KV: rotary embedding + KV append of the preproj output
 };
 
@@ -261,29 +262,33 @@ __device__ __forceinline__ int rope_w_row(int n, int N, int hd) {
 }
 
 // The epilogue: the block's tile goes to LDS as bf16 (the rounding the
-// separate kernel would read); each thread then keeps one 16-column group
-// (one head, 8 frequencies computed once in fp64) and walks rows: q is
+// separate kernel would read; 16-byte chunks XOR-swizzled by row), and behind
+// it the hd/2 frequencies, computed once per block in fp64 (every thread
+// computing its own eight took ~7 us of a 160-row block).  Each thread then
+// keeps one 16-column group (one head, 8 frequencies) and walks rows: q is
 // rotated into the output, k rotated and v copied into the KV cache at the
 // row's (slot, position), 16 bytes per access, both halves of the pairs
 // back at their physical columns.  The k and v columns of the output are not
 // written (attention reads them from the cache).
-template <int BM, int BN, int WGM, int WGN, int WTM, int WTN, int FM, int FN>
-__device__ __forceinline__ void rope_kv_epilogue(const GemmP& p, floatx4 (&acc)[FM][FN], int m0, int n0, int wm,
-                                                 int wn, int lane, int tid) {
+template <int BN>
+__device__ __forceinline__ int rope_tile_chunk(int r, int c) {   // 16-byte chunk c of tile row r
+  constexpr int MASK = (BN / 8) % 8 == 0 ? 7 : 3;          // the XOR stays within the row's chunks
+  static_assert(BN / 8 % (MASK + 1) == 0, "chunks per row");
+  return r * (BN / 8) + (c ^ (r & MASK));
+}
+template <int BM, int BN>
+__device__ __forceinline__ double* rope_thetas() {
   extern __shared__ uint4 lds[];
-  bf16* t = reinterpret_cast<bf16*>(lds);                  // [BM][BN] bf16
-#pragma unroll
-  for (int fm = 0; fm < FM; ++fm)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = wm * WTM + fm * 16 + 4 * (lane >> 4) + i;
-#pragma unroll
-      for (int fn = 0; fn < FN; ++fn) t[r * BN + wn * WTN + fn * 16 + (lane & 15)] = f2bf(acc[fm][fn][i]);
-    }
-  lds_read_barrier();                                       // the producers pass their last barrier too
+  return reinterpret_cast<double*>(lds + BM * BN / 8);
+}
+constexpr int ROPE_THETA_BYTES = 64 * 8;                  // head_dim up to 128
+
+template <int BM, int BN, int NT>
+__device__ __forceinline__ void rope_kv_walk(const GemmP& p, int m0, int n0, int tid) {
+  extern __shared__ uint4 lds[];
   constexpr int JG = BN / 16;                               // 16-column groups per tile row
-  constexpr int RS = (64 * WGM * WGN) / JG;                 // rows in flight
-  static_assert(BN % 16 == 0 && RS > 0, "16-column groups");
+  constexpr int RS = NT / JG;                               // rows in flight
+  static_assert(RS > 0, "16-column groups");
   const int j = tid % JG, r0 = tid / JG;
   const int n = n0 + 16 * j;
   if (r0 >= RS || n >= p.N) return;
@@ -294,17 +299,16 @@ __device__ __forceinline__ void rope_kv_epilogue(const GemmP& p, floatx4 (&acc)[
   const bool rot = part < 2 && a.rope;
   double theta[8];
   if (rot) {
-    const double lb = log2((double)a.base);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) theta[e] = rope_theta(d0 + e, hd, lb);
+    for (int e = 0; e < 8; ++e) theta[e] = rope_thetas<BM, BN>()[d0 + e];
   }
   bf16* cache = reinterpret_cast<bf16*>(a.kv_layer);
   const size_t kv_off = (part == 2 ? a.st.kv : 0) + (size_t)head * a.st.head;
   for (int r = r0; r < BM; r += RS) {
     const int row = m0 + r;
     if (row >= p.M) break;
-    uint4 lo = *reinterpret_cast<const uint4*>(t + r * BN + 16 * j);
-    uint4 hi = *reinterpret_cast<const uint4*>(t + r * BN + 16 * j + 8);
+    uint4 lo = lds[rope_tile_chunk<BN>(r, 2 * j)];
+    uint4 hi = lds[rope_tile_chunk<BN>(r, 2 * j + 1)];
     const int slot = a.row_slot[row], pos = a.row_pos[row];
     if (rot) {
       float x0[8], x1[8];
@@ -355,7 +359,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
   static_assert(BM % 8 == 0 && BN % 8 == 0 && ILO > 0, "8-row groups");
   static_assert(WTM % 16 == 0 && WTN % 16 == 0 && (EPI != EPI_SWIGLU || FN % 2 == 0), "wave tile");
   static_assert((S - 2) * IHI < 64 && S >= 2, "stages");
-  static_assert(BM * BN * 2 <= S * ROWS * 128, "the RoPE epilogue stages the bf16 tile in the ring's LDS");
+  static_assert(BM * BN * 2 + ROPE_THETA_BYTES <= S * ROWS * 128, "the RoPE epilogue stages the bf16 tile in the ring's LDS");
   extern __shared__ uint4 lds[];                 // [S][ROWS * 8] 16-byte chunks
 
   const int per = gridDim.x / 8;
@@ -493,7 +497,22 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
   }
 
   if constexpr (EPI == EPI_ROPE_KV) {
-    rope_kv_epilogue<BM, BN, WGM, WGN, WTM, WTN, FM, FN>(p, acc, m0, tile_n * BN, wm, wn, lane, tid);
+    bf16* t16 = reinterpret_cast<bf16*>(lds);
+#pragma unroll
+    for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = wm * WTM + fm * 16 + 4 * (lane >> 4) + i;
+#pragma unroll
+        for (int fn = 0; fn < FN; ++fn) {
+          const int c = wn * WTN + fn * 16 + (lane & 15);
+          t16[rope_tile_chunk<BN>(r, c >> 3) * 8 + (c & 7)] = f2bf(acc[fm][fn][i]);
+        }
+      }
+    if (p.rope.rope && tid < p.rope.hd / 2)
+      rope_thetas<BM, BN>()[tid] = rope_theta(tid, p.rope.hd, log2((double)p.rope.base));
+    lds_read_barrier();                  // the producers pass their last barrier too
+    rope_kv_walk<BM, BN, 64 * NC>(p, m0, tile_n * BN, tid);
     return;
   }
 #pragma unroll
@@ -517,6 +536,283 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
           const int c = n0_out + wn * WTN + fn * 16 + (lane & 15);
           if (c < p.N) epi_store<T, EPI>(p, r, c, acc[fm][fn][i], split);
         }
+      }
+    }
+  }
+}
+
+// ============================================================================ bf16 MFMA, quadrant tiles
+// Large batches (192 and 256 rows by 256 W rows per block).  At these shapes
+// the matrix cores are the bound, and the chip's power: with operands resident
+// the 256 x 256 loop runs at 97% of the matrix issue rate, at the ~1.8 GHz
+// that the power limit leaves (1400 TFLOP/s; a large library product measures
+// 1261 here).  What the smaller tiles lack is operand feed: a CU keeps ~45 KB
+// of loads in flight, ~30 bytes per clock at HBM latency, and 160 x 256 needs
+// 41 per matrix clock where 256 x 256 needs 32.
+//
+// 8 waves of WGM x WGN, no producers (the accumulators and two halves of each
+// operand fill the 256 registers that two waves per SIMD leave).  A k-tile of
+// 64 is two half stages: rows of every wave's first row half and column half
+// (A0, B0), then the second halves (A1, B1), two stages in LDS.  The wave
+// multiplies the quadrants A0B0, A0B1 | A1B1, A1B0, reading each half from LDS
+// while the quadrant before it runs, so a half stage is free as soon as it is
+// in registers: with one barrier per two quadrants its successor is requested
+// 1.5 k-tiles ahead of its use (a plain two-stage ring, 0.75 ahead, ran 143 us
+// where this runs 121 on 1024 x 15360 x 5120; 160 x 256 producer tiles 158).
+//
+// Hazards, for half stage (kt, h): requested after the barrier that follows
+// the reads of (kt - 2, h) by every wave; read after every wave waited for its
+// own requests (all but the newest two half stages) and passed a barrier.
+// Requests past the last k-tile re-read it into stages that nothing reads.
+//
+// The products take W as the first operand, so a lane holds four consecutive
+// columns of one row: 8- and 16-byte stores.
+template <int N>
+__device__ __forceinline__ void pin_regs(u32x4 (&r)[N]) {   // no use of r moves above this point
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(r[i]));
+}
+// LDS reads as inline assembly with the waits written out: the compiler would
+// take them to overlap the half stages that LDS DMA fills and drain those.
+template <int OFF>
+__device__ __forceinline__ u32x4 lds_read16(uint32_t addr) {
+  u32x4 v;
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "i"(OFF));
+  return v;
+}
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(f);
+  }
+}
+
+// Four consecutive columns c .. c + 3 of row r.
+template <int EPI>
+__device__ __forceinline__ void epi_store4(const GemmP& p, int r, int c, const floatx4& v, int split) {
+  if (p.vec4) {
+    const size_t idx = (size_t)r * p.N + c;
+    if (EPI == EPI_PARTIAL) {
+      *reinterpret_cast<floatx4*>(reinterpret_cast<float*>(p.out) + (size_t)split * p.M * p.N + idx) = v;
+    } else if (EPI == EPI_RESID_TO_F32) {
+      const uint2 x = *reinterpret_cast<const uint2*>(reinterpret_cast<const bf16*>(p.resid) + idx);
+      *reinterpret_cast<floatx4*>(reinterpret_cast<float*>(p.out) + idx) =
+          floatx4{__uint_as_float(x.x << 16) + v[0], __uint_as_float(x.x & 0xffff0000u) + v[1],
+                  __uint_as_float(x.y << 16) + v[2], __uint_as_float(x.y & 0xffff0000u) + v[3]};
+    } else {
+      float f[4];
+      floatx4 x = v;
+      if (EPI == EPI_RESIDF32_TO_ACT) x = *reinterpret_cast<const floatx4*>(reinterpret_cast<const float*>(p.resid) + idx) + v;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) f[i] = EPI == EPI_GELU ? gelu_f(x[i]) : x[i];
+      *reinterpret_cast<uint2*>(reinterpret_cast<bf16*>(p.out) + idx) =
+          make_uint2((uint32_t)f2bf(f[0]) | ((uint32_t)f2bf(f[1]) << 16),
+                     (uint32_t)f2bf(f[2]) | ((uint32_t)f2bf(f[3]) << 16));
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (c + i < p.N) epi_store<bf16, EPI>(p, r, c + i, v[i], split);
+  }
+}
+
+template <int WGM, int WGN, int FMH, int FNH, int EPI>
+__global__ __launch_bounds__(512, 2) void gemm_quad_kernel(GemmP p) {
+  constexpr int BM = WGM * 2 * FMH * 16, BN = WGN * 2 * FNH * 16, BK = 64;
+  constexpr int WTM = BM / WGM, WTN = BN / WGN;
+  constexpr int AH = BM / 2, BH = BN / 2;           // rows of A and of W per half stage
+  constexpr int HG = (AH + BH) / 8;                 // 1 KB requests (8 rows) per half stage
+  constexpr int IHI = (HG + 7) / 8, ILO = HG / 8, RHI = HG % 8;
+  constexpr int HB = (AH + BH) * 8;                 // 16-byte chunks per half stage
+  constexpr int QN = 2 * FMH * FNH;                 // products per quadrant
+  static_assert(WGM * WGN == 8 && AH % 8 == 0 && BH % 8 == 0, "waves and request rows");
+  static_assert(QN >= 2 * FNH + 2 * FMH && QN / 2 >= IHI, "a quadrant carries its reads and requests");
+  static_assert(2 * IHI < 64, "vmcnt range");
+  extern __shared__ uint4 lds[];                    // [stage][half][A rows, W rows][8] 16-byte chunks
+  const int per = gridDim.x / 8;
+  const int t = (blockIdx.x % 8) * per + blockIdx.x / 8;
+  if (t >= p.n_tiles) return;
+  const int tile_m = t % p.tiles_m;
+  const int rest = t / p.tiles_m;
+  const int split = rest % p.n_split;
+  const int tile_n = rest / p.n_split;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WGN, wn = wave % WGN;
+  const int m0 = tile_m * BM;
+  const int n0_out = tile_n * (EPI == EPI_SWIGLU ? BN / 2 : BN);
+  const int kbeg = split * p.k_split;
+  const int kend = min(p.K, kbeg + p.k_split);
+  const int nk = (kend - kbeg) / BK;
+
+  // requests: as gemm_ws_kernel's producers (scalar bases, 32-bit row offsets)
+  const char* A = reinterpret_cast<const char*>(p.A) + (size_t)kbeg * 2;
+  const char* W = reinterpret_cast<const char*>(p.W) + (size_t)kbeg * 2;
+  const int lchunk = (lane & 7) ^ (lane >> 3);
+  const bool extra = wave < RHI;
+  uint32_t off[2][IHI];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int j = 0; j < IHI; ++j) {
+      const int g = min(j * 8 + wave, HG - 1), row = g * 8 + (lane >> 3);
+      size_t r;
+      if (g * 8 < AH) {
+        constexpr int HR = FMH * 16;
+        r = (size_t)min(m0 + (row / HR) * WTM + h * HR + row % HR, p.M - 1);
+      } else {
+        constexpr int HR = FNH * 16;
+        const int q = row - AH, nl = (q / HR) * WTN + h * HR + q % HR;
+        r = EPI == EPI_ROPE_KV ? (size_t)rope_w_row(n0_out + nl, p.N, p.rope.hd)
+                               : (size_t)w_row_of<EPI, WTN>(nl, n0_out, p.N);
+      }
+      off[h][j] = (uint32_t)(r * p.K * 2 + lchunk * 16);
+    }
+  auto request = [&](int kt, int h, int j) {
+    const int g = j * 8 + wave;
+    if (j < ILO || extra)
+      dma16((g * 8 < AH ? A : W) + (size_t)min(kt, nk - 1) * BK * 2 + off[h][j],
+            lds + ((kt & 1) * 2 + h) * HB + g * 64);
+  };
+  auto wait_but = [&](auto nb) {                    // this wave's requests but the newest nb half stages
+    constexpr int NB = decltype(nb)::value;
+    if (extra) wait_vmcnt<NB * IHI>();
+    else wait_vmcnt<NB * ILO>();
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I3 = std::integral_constant<int, 3>;
+
+  floatx4 acc[2 * FMH][2 * FNH];
+#pragma unroll
+  for (int i = 0; i < 2 * FMH; ++i)
+#pragma unroll
+    for (int j = 0; j < 2 * FNH; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const int r16 = lane & 15, cg = lane >> 4;
+  const uint32_t l0 = (uint32_t)(uintptr_t)lds;
+  const uint32_t ao = l0 + (wm * FMH * 16 + r16) * 128, bo = l0 + (AH + wn * FNH * 16 + r16) * 128;
+  const uint32_t x0 = (cg ^ (r16 & 7)) * 16, x1 = ((cg + 4) ^ (r16 & 7)) * 16;
+  const uint32_t a_at[2] = {ao + x0, ao + x1}, b_at[2] = {bo + x0, bo + x1};
+  constexpr uint32_t HALF = HB * 16;
+  u32x4 fa[2][2 * FMH], fb[2][2 * FNH];             // fragments of a half: [k-step][16-row group]
+  auto read_a = [&](int buf, uint32_t half, auto f) {
+    constexpr int F = decltype(f)::value;
+    fa[buf][F] = lds_read16<(F % FMH) * 2048>(a_at[F / FMH] + half);
+  };
+  auto read_b = [&](int buf, uint32_t half, auto f) {
+    constexpr int F = decltype(f)::value;
+    fb[buf][F] = lds_read16<(F % FNH) * 2048>(b_at[F / FNH] + half);
+  };
+  // the products of quadrant (mh, nh), with act(i) issued after product i
+  auto quadrant = [&](const u32x4 (&a)[2 * FMH], const u32x4 (&b)[2 * FNH], auto mh, auto nh, auto&& act) {
+    constexpr int MH = decltype(mh)::value, NH = decltype(nh)::value;
+    static_for<0, QN>([&](auto i) {
+      constexpr int I = decltype(i)::value, ks = I / (FMH * FNH), r = I % (FMH * FNH), fm = r / FNH, fn = r % FNH;
+      floatx4& c = acc[MH * FMH + fm][NH * FNH + fn];
+      c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, b[ks * FNH + fn]),
+                                                  __builtin_bit_cast(bf16x8_t, a[ks * FMH + fm]), c, 0, 0, 0);
+      act(i);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  auto lds_landed = [&]() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
+
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int j = 0; j < IHI; ++j) request(q >> 1, q & 1, j);
+  wait_but(I3{});
+  lds_barrier();
+  static_for<0, 2 * FMH>([&](auto f) { read_a(0, 0, f); });
+  static_for<0, 2 * FNH>([&](auto f) { read_b(0, 0, f); });
+  lds_landed();
+  pin_regs(fa[0]);
+  pin_regs(fb[0]);
+
+  // One k-tile.  A0 is in fa[0] and B0 in fb[P]; B1 is read into fb[1 - P],
+  // A1 into fa[1], then the next tile's A0 into fa[0] and B0 into fb[1 - P].
+  auto tile = [&](int kt, auto pc) {
+    constexpr int P = decltype(pc)::value;
+    const uint32_t cur = (uint32_t)((kt & 1) * 2) * HALF, nxt = (uint32_t)(((kt + 1) & 1) * 2) * HALF;
+    wait_but(I2{});                                 // (kt, 1); newest (kt + 1, 0), (kt + 1, 1)
+    lds_barrier();
+    __builtin_amdgcn_s_setprio(1);
+    quadrant(fa[0], fb[P], I0{}, I0{}, [&](auto i) {
+      constexpr int I = decltype(i)::value;
+      if constexpr (I < 2 * FNH) read_b(1 - P, cur + HALF, i);
+      else if constexpr (I < 2 * FNH + 2 * FMH) read_a(1, cur + HALF, std::integral_constant<int, I - 2 * FNH>{});
+      if constexpr (I % 2 == 1 && I / 2 < IHI) request(kt + 2, 0, I / 2);
+    });
+    lds_landed();
+    pin_regs(fb[1 - P]);
+    pin_regs(fa[1]);
+    quadrant(fa[0], fb[1 - P], I0{}, I1{}, [](auto) {});
+    __builtin_amdgcn_s_setprio(0);
+    wait_but(I2{});                                 // (kt + 1, 0); newest (kt + 1, 1), (kt + 2, 0)
+    lds_barrier();
+    __builtin_amdgcn_s_setprio(1);
+    quadrant(fa[1], fb[1 - P], I1{}, I1{}, [&](auto i) {
+      constexpr int I = decltype(i)::value;
+      if constexpr (I < 2 * FMH) read_a(0, nxt, i);
+      if constexpr (I % 2 == 1 && I / 2 < IHI) request(kt + 2, 1, I / 2);
+    });
+    quadrant(fa[1], fb[P], I1{}, I0{}, [&](auto i) {
+      constexpr int I = decltype(i)::value;
+      if constexpr (I < 2 * FNH) read_b(1 - P, nxt, i);   // past the last tile: stale values, not used
+    });
+    __builtin_amdgcn_s_setprio(0);
+    lds_landed();
+    pin_regs(fa[0]);
+    pin_regs(fb[1 - P]);
+  };
+  for (int kt = 0; kt < nk; kt += 2) {
+    tile(kt, I0{});
+    if (kt + 1 < nk) tile(kt + 1, I1{});
+  }
+  wait_vmcnt<0>();                                  // requests past the end still fill the stages
+
+  // acc[fm][fn][i] = C[row r16][column 4 cg + i] of the 16 x 16 tile
+  if constexpr (EPI == EPI_ROPE_KV) {
+    lds_barrier();                                  // every wave's requests have landed and its reads are done
+    uint2* t8 = reinterpret_cast<uint2*>(lds);
+#pragma unroll
+    for (int fm = 0; fm < 2 * FMH; ++fm)
+#pragma unroll
+      for (int fn = 0; fn < 2 * FNH; ++fn) {
+        const int r = wm * WTM + fm * 16 + r16, c = wn * WTN + fn * 16 + 4 * cg;
+        const floatx4 v = acc[fm][fn];
+        t8[rope_tile_chunk<BN>(r, c >> 3) * 2 + ((c >> 2) & 1)] =
+            make_uint2((uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
+                       (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16));
+      }
+    if (p.rope.rope && tid < p.rope.hd / 2)
+      rope_thetas<BM, BN>()[tid] = rope_theta(tid, p.rope.hd, log2((double)p.rope.base));
+    lds_read_barrier();
+    rope_kv_walk<BM, BN, 512>(p, m0, tile_n * BN, tid);
+    return;
+  }
+#pragma unroll
+  for (int fm = 0; fm < 2 * FMH; ++fm) {
+    const int r = m0 + wm * WTM + fm * 16 + r16;
+    if (r >= p.M) continue;
+    if (EPI == EPI_SWIGLU) {
+      // columns [0, 32) of a wave's 64 are gate rows, [32, 64) the up rows
+#pragma unroll
+      for (int fn = 0; fn < FNH; ++fn) {
+        const int c = n0_out + wn * (WTN / 2) + fn * 16 + 4 * cg;
+        if (c >= p.N) continue;
+        floatx4 v;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = silu_f(acc[fm][fn][i]) * acc[fm][fn + FNH][i];
+        epi_store4<EPI_STORE>(p, r, c, v, 0);
+      }
+    } else {
+#pragma unroll
+      for (int fn = 0; fn < 2 * FNH; ++fn) {
+        const int c = n0_out + wn * WTN + fn * 16 + 4 * cg;
+        if (c < p.N) epi_store4<EPI>(p, r, c, acc[fm][fn], split);
       }
     }
   }
@@ -642,6 +938,18 @@ static hipError_t run_ws(const GemmP& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int WGM, int WGN, int FMH, int FNH, int EPI>
+static hipError_t run_quad(const GemmP& p, hipStream_t s) {
+  // two stages, and room for the RoPE epilogue's frequencies behind its tile
+  const size_t lds_bytes = (size_t)2 * (WGM * FMH + WGN * FNH) * 32 * 128 + ROPE_THETA_BYTES;
+  static std::atomic<uint64_t> lds_set{0};   // devices on which this instance's LDS limit is raised
+  hipError_t e = ensure_dynamic_lds((const void*)gemm_quad_kernel<WGM, WGN, FMH, FNH, EPI>, (int)lds_bytes, lds_set);
+  if (e != hipSuccess) return e;
+  const int grid = (p.n_tiles + 7) / 8 * 8;
+  hipLaunchKernelGGL((gemm_quad_kernel<WGM, WGN, FMH, FNH, EPI>), dim3(grid), dim3(512), lds_bytes, s, p);
+  return hipGetLastError();
+}
+
 template <int BM, int BN, int WGM, int WGN, int PD>
 static hipError_t run_bf16_epi(int epi, const GemmP& p, hipStream_t s) {
   switch (epi) {
@@ -695,8 +1003,9 @@ static int pick_cfg(int M, int n_panels) {
 struct WsTile {
   int bm, bn;
 };
-constexpr WsTile kWsTiles[] = {{64, 64},   {64, 128},  {64, 256},  {96, 128},  {96, 192},
-                               {96, 256},  {160, 128}, {160, 192}, {160, 224}, {160, 256}};
+constexpr WsTile kWsTiles[] = {{64, 64},   {64, 128},  {64, 256},  {96, 128},  {96, 192},  {96, 256},
+                               {160, 128}, {160, 192}, {160, 224}, {160, 256}, {192, 256}, {256, 256}};
+constexpr int kFirstQuadTile = 10;   // the last two run gemm_quad_kernel
 constexpr int kNumWsTiles = sizeof(kWsTiles) / sizeof(kWsTiles[0]);
 
 template <int EPI>
@@ -711,7 +1020,9 @@ static hipError_t run_ws_cfg(int cfg, const GemmP& p, hipStream_t s) {
     case 6: return run_ws<bf16, 160, 128, 2, 4, 4, 4, EPI>(p, s);
     case 7: return run_ws<bf16, 160, 192, 2, 6, 4, 3, EPI>(p, s);
     case 8: return run_ws<bf16, 160, 224, 2, 7, 2, 3, EPI>(p, s);
-    default: return run_ws<bf16, 160, 256, 2, 4, 4, 3, EPI>(p, s);
+    case 9: return run_ws<bf16, 160, 256, 2, 4, 4, 3, EPI>(p, s);
+    case 10: return run_quad<2, 4, 3, 2, EPI>(p, s);
+    default: return run_quad<2, 4, 4, 2, EPI>(p, s);
   }
 }
 
@@ -763,7 +1074,8 @@ static hipError_t run_ws_f32(int epi, int cfg, const GemmP& p, hipStream_t s) {
 // costs ~1.9 ns per A row (L2 hits) and ~3.1 ns per W row when two M-tiles
 // share the W panel (~4.2 ns when one block streams it alone: every row an
 // HBM miss); a block adds ~3 us of pipeline fill plus its output writes
-// (~40 GB/s per CU); blocks beyond the first 256 run as another round.  A
+// (~40 GB/s per CU); blocks beyond the first 256 run as another round.  The
+// quadrant kernel's k-tiles take 1.17 us (192 rows) and 1.5 us (256 rows).  A
 // split-K op's reduction pass reads the fp32 partials and writes the result
 // at ~5.5 TB/s.
 struct WsChoice {
@@ -776,10 +1088,12 @@ static WsChoice pick_ws(int M, int N, int K, bool swiglu, int max_split) {
   for (int c = 0; c < kNumWsTiles; ++c) {
     const int bm = kWsTiles[c].bm, bn = kWsTiles[c].bn;
     if (bm == 64 && M > 64) continue;    // 64-row tiles only for short batches
+    if (c >= kFirstQuadTile && M <= 160) continue;
     const int per = swiglu ? bn / 2 : bn;
     const int tiles_m = (M + bm - 1) / bm;
     const long tiles = (long)tiles_m * ((N + per - 1) / per);
-    const double per_k = 1.9e-3 * bm + (tiles_m >= 2 ? 3.1e-3 : 4.2e-3) * bn;   // us per k-tile
+    const double per_k = c >= kFirstQuadTile ? (bm == 256 ? 1.5 : 1.17)
+                                             : 1.9e-3 * bm + (tiles_m >= 2 ? 3.1e-3 : 4.2e-3) * bn;   // us per k-tile
     for (int ns = 1; ns <= max_split; ++ns) {
       const double rounds = (double)((tiles * ns + 255) / 256);
       const double k_tiles = 2.0 * ((nk / 2 + ns - 1) / ns);               // whole pairs per split
@@ -975,6 +1289,7 @@ hipError_t launch_linear(int dtype, const LinearArgs& a, hipStream_t s, int forc
     }
   }
   p.n_tiles = p.tiles_m * p.tiles_n * p.n_split;
+  p.vec4 = a.N % 4 == 0 && ((reinterpret_cast<uintptr_t>(p.out) | reinterpret_cast<uintptr_t>(p.resid)) & 15) == 0;
   // Rotated k order for the two M-tiles of a W panel, when a block runs at
   // most 192 k-tiles.  Measured in the layers: LLaMA-13B preproj -13% and
   // ffn_ln1 -2%; LLaMA-33B at 288 rows every op -2..-5% (layer -4%); GPT-3
@@ -982,7 +1297,7 @@ hipError_t launch_linear(int dtype, const LinearArgs& a, hipStream_t s, int forc
   // (384 k-tiles per split) +6%.  Four M-tiles: no gain.
   {
     const int nk_block = (n_split > 1 ? p.k_split : a.K) / 64;
-    p.rotate_k = (ws && p.tiles_m == 2 && nk_block <= 192) ? 1 : 0;
+    p.rotate_k = (ws && cfg < kFirstQuadTile && p.tiles_m == 2 && nk_block <= 192) ? 1 : 0;
   }
   if (plan) {
     *plan = LinearPlan{BM, BN, p.n_split};

@@ -1,0 +1,82 @@
+"""Edges of the linear ops' matrix-core kernels through the C-ABI: the large
+bf16 tiles (192 x 256 and 256 x 256) at one to three k-tiles, rows around the
+tile height, column counts that are no multiple of four and an output that is
+not 16-byte aligned; the fp32 tiles at K tails and partial tiles.
+
+Tolerances: bf16 results are one rounding (2^-9) from an fp32 sum whose terms
+the test keeps at |x w| <= ~0.5, so 1e-2 of the largest output; fp32 sums of K
+<= 2048 terms are within K^0.5 2^-24 of it per unit, 2e-5 with room."""
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from paper_2308_16369_amd import sarathi as S  # noqa: E402
+
+
+def _ref(kind, x, w, resid, N):
+    z = x.double().cpu() @ w.double().cpu().t()
+    if kind == S.LINEAR_SWIGLU:
+        return torch.nn.functional.silu(z[:, :N]) * z[:, N:]
+    if kind == S.LINEAR_GELU:
+        return torch.nn.functional.gelu(z)
+    return z + resid.double().cpu() if resid is not None else z
+
+
+def _inputs(kind, M, N, K, dt, seed):
+    g = torch.Generator().manual_seed(seed)
+    x = torch.randn(M, K, generator=g).to(dt)
+    w = (torch.randn(2 * N if kind == S.LINEAR_SWIGLU else N, K, generator=g) * 0.05).to(dt)
+    resid = None
+    if kind in (S.LINEAR_RESID, S.LINEAR_RESID_F32IN):
+        resid = torch.randn(M, N, generator=g).to(dt if kind == S.LINEAR_RESID else torch.float32)
+    return x, w, resid
+
+
+def _err(got, ref):
+    return float((got.double().cpu() - ref).abs().max() / ref.abs().max())
+
+
+KINDS = [S.LINEAR_PLAIN, S.LINEAR_RESID, S.LINEAR_RESID_F32IN, S.LINEAR_SWIGLU, S.LINEAR_GELU]
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("mnk", [(1, 4, 64), (255, 260, 128), (257, 515, 192), (193, 129, 448)])
+@pytest.mark.parametrize("tile", [(192, 256), (256, 256)])
+def test_quad_tile_edges(tile, mnk, shift):
+    M, N, K = mnk
+    index = [S.sarathi_linear_tile_shape(t) for t in range(S.sarathi_linear_tile_count())].index(tile)
+    scratch = torch.empty(S.sarathi_linear_scratch_bytes(M, N), dtype=torch.uint8, device="cuda")
+    for kind in KINDS:
+        x, w, resid = _inputs(kind, M, N, K, torch.bfloat16, M + N + K + kind)
+        xd, wd, rd = x.cuda(), w.cuda(), None if resid is None else resid.cuda()
+        odt = torch.float32 if kind == S.LINEAR_RESID else torch.bfloat16
+        for n_split in (1, 3) if resid is not None else (1,):
+            # one element past the end and before the start stay untouched
+            buf = torch.full((M * N + 2 + shift,), 7.0, dtype=odt, device="cuda")
+            out = buf[shift:shift + M * N]
+            S.sarathi_linear_tiled(kind, M, N, K, xd.data_ptr(), wd.data_ptr(), 0 if rd is None else rd.data_ptr(),
+                                   out.data_ptr(), scratch.data_ptr(), scratch.numel(), index, n_split,
+                                   torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+            assert _err(out.view(M, N), _ref(kind, x, w, resid, N)) <= 1e-2, (kind, n_split)
+            assert bool((buf[:shift] == 7.0).all()) and bool((buf[shift + M * N:] == 7.0).all()), (kind, n_split)
+
+
+@pytest.mark.parametrize("mnk", [(33, 65, 40), (97, 129, 104), (161, 1100, 72), (8, 33, 2048), (1030, 260, 136)])
+def test_f32_tile_edges(mnk):
+    M, N, K = mnk
+    scratch = torch.empty(S.sarathi_linear_scratch_bytes(M, N), dtype=torch.uint8, device="cuda")
+    for kind in KINDS:
+        x, w, resid = _inputs(kind, M, N, K, torch.float32, M + N + K + kind)
+        # the last row's and the last weight row's tails end the buffers: what lies behind them is not read as data
+        xd = torch.cat([x.flatten(), torch.full((64,), float("nan"))]).cuda()
+        wd = torch.cat([w.flatten(), torch.full((64,), float("nan"))]).cuda()
+        rd = None if resid is None else resid.cuda()
+        out = torch.empty(M, N, dtype=torch.float32, device="cuda")
+        for scratch_bytes in (scratch.numel(), 0):
+            S.sarathi_linear(S.F32, kind, M, N, K, xd.data_ptr(), wd.data_ptr(), 0 if rd is None else rd.data_ptr(),
+                             out.data_ptr(), scratch.data_ptr() if scratch_bytes else 0, scratch_bytes,
+                             torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+            assert _err(out, _ref(kind, x, w, resid, N)) <= 2e-5, (kind, scratch_bytes)
