@@ -34,7 +34,7 @@ struct GemmP {
                         // rotate their k-tile order
   void* out;            // [M, N]: dtype, or fp32 for EPI_RESID_TO_F32; EPI_PARTIAL: fp32 [n_split][M, N]
   const void* resid;    // EPI_RESID_TO_F32: dtype [M,N]; EPI_RESIDF32_TO_ACT: fp32 [M,N]
-  int vec4;             // N a multiple of 4 and out / resid 16-byte aligned: four columns per store
+  int vec4, vec8;       // N a multiple of 4 / 8 and out, resid 16-byte aligned: wide stores
   RopeArgs rope;        // EPI_ROPE_KV: rotary embedding + KV append of the preproj output
 };
 
@@ -271,7 +271,7 @@ __device__ __forceinline__ int rope_w_row(int n, int N, int hd) {
 // back at their physical columns.  The k and v columns of the output are not
 // written (attention reads them from the cache).
 template <int BN>
-__device__ __forceinline__ int rope_tile_chunk(int r, int c) {   // 16-byte chunk c of tile row r
+__device__ __forceinline__ int tile_chunk(int r, int c) {   // 16-byte chunk c of tile row r
   constexpr int MASK = (BN / 8) % 8 == 0 ? 7 : 3;          // the XOR stays within the row's chunks
   static_assert(BN / 8 % (MASK + 1) == 0, "chunks per row");
   return r * (BN / 8) + (c ^ (r & MASK));
@@ -307,8 +307,8 @@ __device__ __forceinline__ void rope_kv_walk(const GemmP& p, int m0, int n0, int
   for (int r = r0; r < BM; r += RS) {
     const int row = m0 + r;
     if (row >= p.M) break;
-    uint4 lo = lds[rope_tile_chunk<BN>(r, 2 * j)];
-    uint4 hi = lds[rope_tile_chunk<BN>(r, 2 * j + 1)];
+    uint4 lo = lds[tile_chunk<BN>(r, 2 * j)];
+    uint4 hi = lds[tile_chunk<BN>(r, 2 * j + 1)];
     const int slot = a.row_slot[row], pos = a.row_pos[row];
     if (rot) {
       float x0[8], x1[8];
@@ -506,7 +506,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
 #pragma unroll
         for (int fn = 0; fn < FN; ++fn) {
           const int c = wn * WTN + fn * 16 + (lane & 15);
-          t16[rope_tile_chunk<BN>(r, c >> 3) * 8 + (c & 7)] = f2bf(acc[fm][fn][i]);
+          t16[tile_chunk<BN>(r, c >> 3) * 8 + (c & 7)] = f2bf(acc[fm][fn][i]);
         }
       }
     if (p.rope.rope && tid < p.rope.hd / 2)
@@ -588,7 +588,7 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-// Four consecutive columns c .. c + 3 of row r.
+// Four consecutive columns c .. c + 3 of row r (residual kinds and partials).
 template <int EPI>
 __device__ __forceinline__ void epi_store4(const GemmP& p, int r, int c, const floatx4& v, int split) {
   if (p.vec4) {
@@ -601,14 +601,10 @@ __device__ __forceinline__ void epi_store4(const GemmP& p, int r, int c, const f
           floatx4{__uint_as_float(x.x << 16) + v[0], __uint_as_float(x.x & 0xffff0000u) + v[1],
                   __uint_as_float(x.y << 16) + v[2], __uint_as_float(x.y & 0xffff0000u) + v[3]};
     } else {
-      float f[4];
-      floatx4 x = v;
-      if (EPI == EPI_RESIDF32_TO_ACT) x = *reinterpret_cast<const floatx4*>(reinterpret_cast<const float*>(p.resid) + idx) + v;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) f[i] = EPI == EPI_GELU ? gelu_f(x[i]) : x[i];
+      const floatx4 x = *reinterpret_cast<const floatx4*>(reinterpret_cast<const float*>(p.resid) + idx) + v;
       *reinterpret_cast<uint2*>(reinterpret_cast<bf16*>(p.out) + idx) =
-          make_uint2((uint32_t)f2bf(f[0]) | ((uint32_t)f2bf(f[1]) << 16),
-                     (uint32_t)f2bf(f[2]) | ((uint32_t)f2bf(f[3]) << 16));
+          make_uint2((uint32_t)f2bf(x[0]) | ((uint32_t)f2bf(x[1]) << 16),
+                     (uint32_t)f2bf(x[2]) | ((uint32_t)f2bf(x[3]) << 16));
     }
   } else {
 #pragma unroll
@@ -617,19 +613,24 @@ __device__ __forceinline__ void epi_store4(const GemmP& p, int r, int c, const f
   }
 }
 
-template <int WGM, int WGN, int FMH, int FNH, int EPI>
+template <int FM, int FN, int EPI>
 __global__ __launch_bounds__(512, 2) void gemm_quad_kernel(GemmP p) {
-  constexpr int BM = WGM * 2 * FMH * 16, BN = WGN * 2 * FNH * 16, BK = 64;
-  constexpr int WTM = BM / WGM, WTN = BN / WGN;
-  constexpr int AH = BM / 2, BH = BN / 2;           // rows of A and of W per half stage
-  constexpr int HG = (AH + BH) / 8;                 // 1 KB requests (8 rows) per half stage
-  constexpr int IHI = (HG + 7) / 8, ILO = HG / 8, RHI = HG % 8;
-  constexpr int HB = (AH + BH) * 8;                 // 16-byte chunks per half stage
-  constexpr int QN = 2 * FMH * FNH;                 // products per quadrant
-  static_assert(WGM * WGN == 8 && AH % 8 == 0 && BH % 8 == 0, "waves and request rows");
-  static_assert(QN >= 2 * FNH + 2 * FMH && QN / 2 >= IHI, "a quadrant carries its reads and requests");
-  static_assert(2 * IHI < 64, "vmcnt range");
-  extern __shared__ uint4 lds[];                    // [stage][half][A rows, W rows][8] 16-byte chunks
+  constexpr int WGM = 2, WGN = 4, BM = WGM * FM * 16, BN = WGN * FN * 16, BK = 64;
+  constexpr int WTM = FM * 16, WTN = FN * 16;
+  constexpr int FM0 = (FM + 1) / 2, FM1 = FM / 2, FN0 = (FN + 1) / 2, FN1 = FN / 2;   // 16-row groups per half
+  constexpr int AH0 = WGM * FM0 * 16, AH1 = WGM * FM1 * 16, BH0 = WGN * FN0 * 16, BH1 = WGN * FN1 * 16;   // rows
+  constexpr int HG0 = (AH0 + BH0) / 8, HG1 = (AH1 + BH1) / 8;       // 1 KB requests (8 rows) per half stage
+  constexpr int I0H = (HG0 + 7) / 8, I1H = (HG1 + 7) / 8;           // per wave: at most,
+  constexpr int I0L = HG0 / 8, I1L = HG1 / 8;                       // and at least
+  constexpr int Q00 = 2 * FM0 * FN0, Q11 = 2 * FM1 * FN1, Q10 = 2 * FM1 * FN0;   // products of the quadrants
+  static_assert(FM1 > 0 && FN1 > 0, "two halves each way");
+  static_assert(Q00 >= 2 * FN1 + 2 * FM1 && Q11 + Q10 >= 2 * FM0 + 2 * FN0 && Q10 >= 2 * FN0, "reads per phase");
+  static_assert(Q00 / 2 >= I0H && (Q11 + Q10) / 2 >= I1H && I0H + 2 * I1H < 64, "requests per phase");
+  static_assert(HG0 * 1024 + FM0 * 2048 < 65536, "immediate LDS offsets");
+  // [stage][half][AH0 A rows, BH0 W rows][8] 16-byte chunks: a wave's rows start
+  // at the same place in both halves (a smaller second half leaves gaps), so
+  // one LDS address per operand and k-step serves both
+  extern __shared__ uint4 lds[];
   const int per = gridDim.x / 8;
   const int t = (blockIdx.x % 8) * per + blockIdx.x / 8;
   if (t >= p.n_tiles) return;
@@ -650,69 +651,99 @@ __global__ __launch_bounds__(512, 2) void gemm_quad_kernel(GemmP p) {
   const char* A = reinterpret_cast<const char*>(p.A) + (size_t)kbeg * 2;
   const char* W = reinterpret_cast<const char*>(p.W) + (size_t)kbeg * 2;
   const int lchunk = (lane & 7) ^ (lane >> 3);
-  const bool extra = wave < RHI;
-  uint32_t off[2][IHI];
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int j = 0; j < IHI; ++j) {
-      const int g = min(j * 8 + wave, HG - 1), row = g * 8 + (lane >> 3);
-      size_t r;
-      if (g * 8 < AH) {
-        constexpr int HR = FMH * 16;
-        r = (size_t)min(m0 + (row / HR) * WTM + h * HR + row % HR, p.M - 1);
-      } else {
-        constexpr int HR = FNH * 16;
-        const int q = row - AH, nl = (q / HR) * WTN + h * HR + q % HR;
-        r = EPI == EPI_ROPE_KV ? (size_t)rope_w_row(n0_out + nl, p.N, p.rope.hd)
-                               : (size_t)w_row_of<EPI, WTN>(nl, n0_out, p.N);
-      }
-      off[h][j] = (uint32_t)(r * p.K * 2 + lchunk * 16);
+  // SwiGLU: every 16 W rows of the tile are 8 gate rows and their 8 up rows
+  auto w_row = [&](int nl) -> size_t {
+    if (EPI == EPI_ROPE_KV) return rope_w_row(n0_out + nl, p.N, p.rope.hd);
+    if (EPI == EPI_SWIGLU) {
+      const int j = min(n0_out + (nl >> 4) * 8 + (nl & 7), p.N - 1);
+      return (nl & 8) ? p.N + j : j;
     }
-  auto request = [&](int kt, int h, int j) {
+    return min(n0_out + nl, p.N - 1);
+  };
+  auto offset = [&](int h, int j) -> uint32_t {
+    const int ah = h ? AH1 : AH0, arow = (h ? FM1 : FM0) * 16, brow = (h ? FN1 : FN0) * 16;
+    const int g = min(j * 8 + wave, (h ? HG1 : HG0) - 1), row = g * 8 + (lane >> 3);
+    size_t r;
+    if (g * 8 < ah) {
+      r = (size_t)min(m0 + (row / arow) * WTM + (h ? FM0 * 16 : 0) + row % arow, p.M - 1);
+    } else {
+      const int q = row - ah;
+      r = w_row((q / brow) * WTN + (h ? FN0 * 16 : 0) + q % brow);
+    }
+    return (uint32_t)(r * p.K * 2 + lchunk * 16);
+  };
+  uint32_t off0[I0H], off1[I1H];
+#pragma unroll
+  for (int j = 0; j < I0H; ++j) off0[j] = offset(0, j);
+#pragma unroll
+  for (int j = 0; j < I1H; ++j) off1[j] = offset(1, j);
+  constexpr int HALF = HG0 * 64, STAGE = 2 * HALF;  // 16-byte chunks
+  auto request0 = [&](int kt, int j) {
     const int g = j * 8 + wave;
-    if (j < ILO || extra)
-      dma16((g * 8 < AH ? A : W) + (size_t)min(kt, nk - 1) * BK * 2 + off[h][j],
-            lds + ((kt & 1) * 2 + h) * HB + g * 64);
+    if (j < I0L || g < HG0)
+      dma16((g * 8 < AH0 ? A : W) + (size_t)min(kt, nk - 1) * BK * 2 + off0[j], lds + (kt & 1) * STAGE + g * 64);
   };
-  auto wait_but = [&](auto nb) {                    // this wave's requests but the newest nb half stages
-    constexpr int NB = decltype(nb)::value;
-    if (extra) wait_vmcnt<NB * IHI>();
-    else wait_vmcnt<NB * ILO>();
+  auto request1 = [&](int kt, int j) {
+    const int g = j * 8 + wave, row = g * 8;
+    const int at = row < AH1 ? (row / (FM1 * 16)) * (FM0 * 16) + row % (FM1 * 16)
+                             : AH0 + ((row - AH1) / (FN1 * 16)) * (FN0 * 16) + (row - AH1) % (FN1 * 16);
+    if (j < I1L || g < HG1)
+      dma16((row < AH1 ? A : W) + (size_t)min(kt, nk - 1) * BK * 2 + off1[j],
+            lds + (kt & 1) * STAGE + HALF + at * 8);
   };
-  using I0 = std::integral_constant<int, 0>;
-  using I1 = std::integral_constant<int, 1>;
-  using I2 = std::integral_constant<int, 2>;
-  using I3 = std::integral_constant<int, 3>;
+  // this wave's requests but the newest half stage of each kind (EXTRA more half 1s) have landed
+  const bool more0 = wave < HG0 % 8, more1 = wave < HG1 % 8;
+  auto wait_but = [&](auto n1) {
+    constexpr int N1 = decltype(n1)::value;
+    if (more0) {
+      if (more1) wait_vmcnt<I0L + 1 + N1 * (I1L + 1)>();
+      else wait_vmcnt<I0L + 1 + N1 * I1L>();
+    } else {
+      if (more1) wait_vmcnt<I0L + N1 * (I1L + 1)>();
+      else wait_vmcnt<I0L + N1 * I1L>();
+    }
+  };
+  using C0 = std::integral_constant<int, 0>;
+  using C1 = std::integral_constant<int, 1>;
+  using C2 = std::integral_constant<int, 2>;
 
-  floatx4 acc[2 * FMH][2 * FNH];
+  floatx4 acc[FM][FN];
 #pragma unroll
-  for (int i = 0; i < 2 * FMH; ++i)
+  for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int j = 0; j < 2 * FNH; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const int r16 = lane & 15, cg = lane >> 4;
+    for (int j = 0; j < FN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
   const uint32_t l0 = (uint32_t)(uintptr_t)lds;
-  const uint32_t ao = l0 + (wm * FMH * 16 + r16) * 128, bo = l0 + (AH + wn * FNH * 16 + r16) * 128;
-  const uint32_t x0 = (cg ^ (r16 & 7)) * 16, x1 = ((cg + 4) ^ (r16 & 7)) * 16;
-  const uint32_t a_at[2] = {ao + x0, ao + x1}, b_at[2] = {bo + x0, bo + x1};
-  constexpr uint32_t HALF = HB * 16;
-  u32x4 fa[2][2 * FMH], fb[2][2 * FNH];             // fragments of a half: [k-step][16-row group]
-  auto read_a = [&](int buf, uint32_t half, auto f) {
+  const uint32_t ax = l0 + (wm * FM0 * 16 + (lane & 15)) * 128 + ((lane >> 4) ^ (lane & 7)) * 16;
+  const uint32_t bx = ax + (AH0 + wn * FN0 * 16 - wm * FM0 * 16) * 128;
+  // k-step 0 and 1 of a row (chunks 0-3 and 4-7: bit 6 of the swizzled address)
+  const uint32_t a_at[2] = {ax, ax ^ 64u}, b_at[2] = {bx, bx ^ 64u};
+  constexpr int HOFF = HALF * 16;
+  u32x4 fa[2][2 * FM0], fb[2][2 * FN0];             // fragments of a half: [k-step][16-row group]
+  auto read_a0 = [&](uint32_t st, auto f) {
     constexpr int F = decltype(f)::value;
-    fa[buf][F] = lds_read16<(F % FMH) * 2048>(a_at[F / FMH] + half);
+    fa[0][F] = lds_read16<(F % FM0) * 2048>(a_at[F / FM0] + st);
   };
-  auto read_b = [&](int buf, uint32_t half, auto f) {
+  auto read_a1 = [&](uint32_t st, auto f) {
     constexpr int F = decltype(f)::value;
-    fb[buf][F] = lds_read16<(F % FNH) * 2048>(b_at[F / FNH] + half);
+    fa[1][F] = lds_read16<HOFF + (F % FM1) * 2048>(a_at[F / FM1] + st);
+  };
+  auto read_b0 = [&](u32x4 (&d)[2 * FN0], uint32_t st, auto f) {
+    constexpr int F = decltype(f)::value;
+    d[F] = lds_read16<(F % FN0) * 2048>(b_at[F / FN0] + st);
+  };
+  auto read_b1 = [&](u32x4 (&d)[2 * FN0], uint32_t st, auto f) {
+    constexpr int F = decltype(f)::value;
+    d[F] = lds_read16<HOFF + (F % FN1) * 2048>(b_at[F / FN1] + st);
   };
   // the products of quadrant (mh, nh), with act(i) issued after product i
-  auto quadrant = [&](const u32x4 (&a)[2 * FMH], const u32x4 (&b)[2 * FNH], auto mh, auto nh, auto&& act) {
+  auto quadrant = [&](const u32x4* a, const u32x4* b, auto mh, auto nh, auto&& act) {
     constexpr int MH = decltype(mh)::value, NH = decltype(nh)::value;
-    static_for<0, QN>([&](auto i) {
-      constexpr int I = decltype(i)::value, ks = I / (FMH * FNH), r = I % (FMH * FNH), fm = r / FNH, fn = r % FNH;
-      floatx4& c = acc[MH * FMH + fm][NH * FNH + fn];
-      c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, b[ks * FNH + fn]),
-                                                  __builtin_bit_cast(bf16x8_t, a[ks * FMH + fm]), c, 0, 0, 0);
+    constexpr int QM = MH ? FM1 : FM0, QW = NH ? FN1 : FN0;
+    static_for<0, 2 * QM * QW>([&](auto i) {
+      constexpr int I = decltype(i)::value, ks = I / (QM * QW), r = I % (QM * QW), fm = r / QW, fn = r % QW;
+      floatx4& c = acc[MH * FM0 + fm][NH * FN0 + fn];
+      c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, b[ks * QW + fn]),
+                                                  __builtin_bit_cast(bf16x8_t, a[ks * QM + fm]), c, 0, 0, 0);
       act(i);
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -720,13 +751,16 @@ __global__ __launch_bounds__(512, 2) void gemm_quad_kernel(GemmP p) {
   auto lds_landed = [&]() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
 
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
+  for (int kt = 0; kt < 2; ++kt) {
 #pragma unroll
-    for (int j = 0; j < IHI; ++j) request(q >> 1, q & 1, j);
-  wait_but(I3{});
+    for (int j = 0; j < I0H; ++j) request0(kt, j);
+#pragma unroll
+    for (int j = 0; j < I1H; ++j) request1(kt, j);
+  }
+  wait_but(C2{});                                   // (0, 0); newest (0, 1), (1, 0), (1, 1)
   lds_barrier();
-  static_for<0, 2 * FMH>([&](auto f) { read_a(0, 0, f); });
-  static_for<0, 2 * FNH>([&](auto f) { read_b(0, 0, f); });
+  static_for<0, 2 * FM0>([&](auto f) { read_a0(0, f); });
+  static_for<0, 2 * FN0>([&](auto f) { read_b0(fb[0], 0, f); });
   lds_landed();
   pin_regs(fa[0]);
   pin_regs(fb[0]);
@@ -735,32 +769,35 @@ __global__ __launch_bounds__(512, 2) void gemm_quad_kernel(GemmP p) {
   // A1 into fa[1], then the next tile's A0 into fa[0] and B0 into fb[1 - P].
   auto tile = [&](int kt, auto pc) {
     constexpr int P = decltype(pc)::value;
-    const uint32_t cur = (uint32_t)((kt & 1) * 2) * HALF, nxt = (uint32_t)(((kt + 1) & 1) * 2) * HALF;
-    wait_but(I2{});                                 // (kt, 1); newest (kt + 1, 0), (kt + 1, 1)
+    const uint32_t cur = (uint32_t)(kt & 1) * (STAGE * 16), nxt = (uint32_t)((kt + 1) & 1) * (STAGE * 16);
+    wait_but(C1{});                                 // (kt, 1); newest (kt + 1, 0), (kt + 1, 1)
     lds_barrier();
     __builtin_amdgcn_s_setprio(1);
-    quadrant(fa[0], fb[P], I0{}, I0{}, [&](auto i) {
+    quadrant(fa[0], fb[P], C0{}, C0{}, [&](auto i) {
       constexpr int I = decltype(i)::value;
-      if constexpr (I < 2 * FNH) read_b(1 - P, cur + HALF, i);
-      else if constexpr (I < 2 * FNH + 2 * FMH) read_a(1, cur + HALF, std::integral_constant<int, I - 2 * FNH>{});
-      if constexpr (I % 2 == 1 && I / 2 < IHI) request(kt + 2, 0, I / 2);
+      if constexpr (I < 2 * FN1) read_b1(fb[1 - P], cur, i);
+      else if constexpr (I < 2 * FN1 + 2 * FM1) read_a1(cur, std::integral_constant<int, I - 2 * FN1>{});
+      if constexpr (I % 2 == 1 && I / 2 < I0H) request0(kt + 2, I / 2);
     });
     lds_landed();
     pin_regs(fb[1 - P]);
     pin_regs(fa[1]);
-    quadrant(fa[0], fb[1 - P], I0{}, I1{}, [](auto) {});
+    quadrant(fa[0], fb[1 - P], C0{}, C1{}, [](auto) {});
     __builtin_amdgcn_s_setprio(0);
-    wait_but(I2{});                                 // (kt + 1, 0); newest (kt + 1, 1), (kt + 2, 0)
+    wait_but(C1{});                                 // (kt + 1, 0); newest (kt + 1, 1), (kt + 2, 0)
     lds_barrier();
     __builtin_amdgcn_s_setprio(1);
-    quadrant(fa[1], fb[1 - P], I1{}, I1{}, [&](auto i) {
+    quadrant(fa[1], fb[1 - P], C1{}, C1{}, [&](auto i) {
       constexpr int I = decltype(i)::value;
-      if constexpr (I < 2 * FMH) read_a(0, nxt, i);
-      if constexpr (I % 2 == 1 && I / 2 < IHI) request(kt + 2, 1, I / 2);
+      if constexpr (I < 2 * FM0) read_a0(nxt, i);
+      if constexpr (I % 2 == 1 && I / 2 < I1H) request1(kt + 2, I / 2);
     });
-    quadrant(fa[1], fb[P], I1{}, I0{}, [&](auto i) {
-      constexpr int I = decltype(i)::value;
-      if constexpr (I < 2 * FNH) read_b(1 - P, nxt, i);   // past the last tile: stale values, not used
+    // past the last tile the reads return stale values, which are not used
+    quadrant(fa[1], fb[P], C1{}, C0{}, [&](auto i) {
+      constexpr int I = decltype(i)::value, LEFT = 2 * FM0 > Q11 ? 2 * FM0 - Q11 : 0, J = Q11 + I;
+      if constexpr (I < LEFT) read_a0(nxt, std::integral_constant<int, (I < LEFT ? Q11 + I : 0)>{});
+      else if constexpr (I - LEFT < 2 * FN0) read_b0(fb[1 - P], nxt, std::integral_constant<int, I - LEFT>{});
+      if constexpr (J % 2 == 1 && J / 2 < I1H) request1(kt + 2, J / 2);
     });
     __builtin_amdgcn_s_setprio(0);
     lds_landed();
@@ -768,52 +805,85 @@ __global__ __launch_bounds__(512, 2) void gemm_quad_kernel(GemmP p) {
     pin_regs(fb[1 - P]);
   };
   for (int kt = 0; kt < nk; kt += 2) {
-    tile(kt, I0{});
-    if (kt + 1 < nk) tile(kt + 1, I1{});
+    tile(kt, C0{});
+    if (kt + 1 < nk) tile(kt + 1, C1{});
   }
   wait_vmcnt<0>();                                  // requests past the end still fill the stages
 
-  // acc[fm][fn][i] = C[row r16][column 4 cg + i] of the 16 x 16 tile
-  if constexpr (EPI == EPI_ROPE_KV) {
+  // acc[fm][fn][i] = C[row r16][column 4 cg + i] of the 16 x 16 tile.  (The lane
+  // is taken anew: it needs no register through the loop.)
+  const int le = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), te = wave * 64 + le;
+  const int r16 = le & 15, cg = le >> 4;
+  if constexpr (EPI == EPI_ROPE_KV || EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_SWIGLU) {
+    // bf16 results go to LDS and leave in whole rows, 16 bytes per lane
+    // (storing from the registers writes 16- and 32-byte pieces of a line:
+    // +14 us on the 1021-row ffn_ln1)
+    constexpr int BO = EPI == EPI_SWIGLU ? BN / 2 : BN;
     lds_barrier();                                  // every wave's requests have landed and its reads are done
-    uint2* t8 = reinterpret_cast<uint2*>(lds);
 #pragma unroll
-    for (int fm = 0; fm < 2 * FMH; ++fm)
+    for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
-      for (int fn = 0; fn < 2 * FNH; ++fn) {
-        const int r = wm * WTM + fm * 16 + r16, c = wn * WTN + fn * 16 + 4 * cg;
-        const floatx4 v = acc[fm][fn];
-        t8[rope_tile_chunk<BN>(r, c >> 3) * 2 + ((c >> 2) & 1)] =
-            make_uint2((uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
-                       (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16));
+      for (int fn = 0; fn < FN; ++fn) {
+        const int r = wm * WTM + fm * 16 + r16;
+        floatx4 v = acc[fm][fn];
+        if constexpr (EPI == EPI_SWIGLU) {
+          // columns 0-7 (lanes 0-31) are gate rows, 8-15 (lane + 32) their up
+          // rows; swapping halves gives lanes 0-31 both of columns 4 (cg & 1)
+          // and + 1, lanes 32-63 both of + 2 and + 3
+          float m[2];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const auto gu = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 2]), false,
+                                                             false);
+            m[i] = silu_f(__uint_as_float(gu[0])) * __uint_as_float(gu[1]);
+          }
+          const int c = (wn * FN + fn) * 8 + 4 * (cg & 1) + (cg & 2);
+          reinterpret_cast<uint32_t*>(lds)[tile_chunk<BO>(r, c >> 3) * 4 + ((c >> 1) & 3)] =
+              (uint32_t)f2bf(m[0]) | ((uint32_t)f2bf(m[1]) << 16);
+        } else {
+          if (EPI == EPI_GELU) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = gelu_f(v[i]);
+          }
+          const int c = wn * WTN + fn * 16 + 4 * cg;
+          reinterpret_cast<uint2*>(lds)[tile_chunk<BO>(r, c >> 3) * 2 + ((c >> 2) & 1)] =
+              make_uint2((uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
+                         (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16));
+        }
       }
-    if (p.rope.rope && tid < p.rope.hd / 2)
-      rope_thetas<BM, BN>()[tid] = rope_theta(tid, p.rope.hd, log2((double)p.rope.base));
+    if (EPI == EPI_ROPE_KV && p.rope.rope && te < p.rope.hd / 2)
+      rope_thetas<BM, BN>()[te] = rope_theta(te, p.rope.hd, log2((double)p.rope.base));
     lds_read_barrier();
-    rope_kv_walk<BM, BN, 512>(p, m0, tile_n * BN, tid);
+    if constexpr (EPI == EPI_ROPE_KV) {
+      rope_kv_walk<BM, BN, 512>(p, m0, tile_n * BN, te);
+    } else {
+      constexpr int CH = BO / 8;                    // 16-byte chunks per row
+      bf16* out = reinterpret_cast<bf16*>(p.out);
+      for (int i = te; i < BM * CH; i += 512) {
+        const int r = i / CH, c = i % CH;
+        const int row = m0 + r, col = n0_out + 8 * c;
+        if (row >= p.M || col >= p.N) continue;
+        const uint4 v = lds[tile_chunk<BO>(r, c)];
+        bf16* dst = out + (size_t)row * p.N + col;
+        if (p.vec8) {
+          *reinterpret_cast<uint4*>(dst) = v;
+        } else {
+          const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (col + e < p.N) dst[e] = (bf16)(w[e / 2] >> (16 * (e & 1)));
+        }
+      }
+    }
     return;
   }
 #pragma unroll
-  for (int fm = 0; fm < 2 * FMH; ++fm) {
+  for (int fm = 0; fm < FM; ++fm) {
     const int r = m0 + wm * WTM + fm * 16 + r16;
-    if (r >= p.M) continue;
-    if (EPI == EPI_SWIGLU) {
-      // columns [0, 32) of a wave's 64 are gate rows, [32, 64) the up rows
 #pragma unroll
-      for (int fn = 0; fn < FNH; ++fn) {
-        const int c = n0_out + wn * (WTN / 2) + fn * 16 + 4 * cg;
-        if (c >= p.N) continue;
-        floatx4 v;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = silu_f(acc[fm][fn][i]) * acc[fm][fn + FNH][i];
-        epi_store4<EPI_STORE>(p, r, c, v, 0);
-      }
-    } else {
-#pragma unroll
-      for (int fn = 0; fn < 2 * FNH; ++fn) {
-        const int c = n0_out + wn * WTN + fn * 16 + 4 * cg;
-        if (c < p.N) epi_store4<EPI>(p, r, c, acc[fm][fn], split);
-      }
+    for (int fn = 0; fn < FN; ++fn) {
+      const int c = n0_out + wn * WTN + fn * 16 + 4 * cg;
+      if (r < p.M && c < p.N) epi_store4<EPI>(p, r, c, acc[fm][fn], split);
     }
   }
 }
@@ -938,15 +1008,17 @@ static hipError_t run_ws(const GemmP& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int WGM, int WGN, int FMH, int FNH, int EPI>
+template <int FM, int FN, int EPI>
 static hipError_t run_quad(const GemmP& p, hipStream_t s) {
-  // two stages, and room for the RoPE epilogue's frequencies behind its tile
-  const size_t lds_bytes = (size_t)2 * (WGM * FMH + WGN * FNH) * 32 * 128 + ROPE_THETA_BYTES;
+  // two stages of two halves, and room for the RoPE epilogue's frequencies
+  // behind its tile
+  constexpr int ROWS0 = (2 * ((FM + 1) / 2) + 4 * ((FN + 1) / 2)) * 16;   // rows of a half stage
+  const size_t lds_bytes = (size_t)4 * ROWS0 * 128 + ROPE_THETA_BYTES;
   static std::atomic<uint64_t> lds_set{0};   // devices on which this instance's LDS limit is raised
-  hipError_t e = ensure_dynamic_lds((const void*)gemm_quad_kernel<WGM, WGN, FMH, FNH, EPI>, (int)lds_bytes, lds_set);
+  hipError_t e = ensure_dynamic_lds((const void*)gemm_quad_kernel<FM, FN, EPI>, (int)lds_bytes, lds_set);
   if (e != hipSuccess) return e;
   const int grid = (p.n_tiles + 7) / 8 * 8;
-  hipLaunchKernelGGL((gemm_quad_kernel<WGM, WGN, FMH, FNH, EPI>), dim3(grid), dim3(512), lds_bytes, s, p);
+  hipLaunchKernelGGL((gemm_quad_kernel<FM, FN, EPI>), dim3(grid), dim3(512), lds_bytes, s, p);
   return hipGetLastError();
 }
 
@@ -1004,8 +1076,10 @@ struct WsTile {
   int bm, bn;
 };
 constexpr WsTile kWsTiles[] = {{64, 64},   {64, 128},  {64, 256},  {96, 128},  {96, 192},  {96, 256},
-                               {160, 128}, {160, 192}, {160, 224}, {160, 256}, {192, 256}, {256, 256}};
-constexpr int kFirstQuadTile = 10;   // the last two run gemm_quad_kernel
+                               {160, 128}, {160, 192}, {160, 224}, {160, 256}, {288, 192}, {192, 256},
+                               {256, 256}};
+constexpr int kFirstQuadTile = 10;   // the rest run gemm_quad_kernel
+constexpr double kQuadTileUs[] = {1.27, 1.17, 1.5};   // their time per 64-wide k-tile
 constexpr int kNumWsTiles = sizeof(kWsTiles) / sizeof(kWsTiles[0]);
 
 template <int EPI>
@@ -1021,8 +1095,9 @@ static hipError_t run_ws_cfg(int cfg, const GemmP& p, hipStream_t s) {
     case 7: return run_ws<bf16, 160, 192, 2, 6, 4, 3, EPI>(p, s);
     case 8: return run_ws<bf16, 160, 224, 2, 7, 2, 3, EPI>(p, s);
     case 9: return run_ws<bf16, 160, 256, 2, 4, 4, 3, EPI>(p, s);
-    case 10: return run_quad<2, 4, 3, 2, EPI>(p, s);
-    default: return run_quad<2, 4, 4, 2, EPI>(p, s);
+    case 10: return run_quad<9, 3, EPI>(p, s);
+    case 11: return run_quad<6, 4, EPI>(p, s);
+    default: return run_quad<8, 4, EPI>(p, s);
   }
 }
 
@@ -1075,7 +1150,7 @@ static hipError_t run_ws_f32(int epi, int cfg, const GemmP& p, hipStream_t s) {
 // share the W panel (~4.2 ns when one block streams it alone: every row an
 // HBM miss); a block adds ~3 us of pipeline fill plus its output writes
 // (~40 GB/s per CU); blocks beyond the first 256 run as another round.  The
-// quadrant kernel's k-tiles take 1.17 us (192 rows) and 1.5 us (256 rows).  A
+// quadrant kernel's k-tiles are priced by measurement.  A
 // split-K op's reduction pass reads the fp32 partials and writes the result
 // at ~5.5 TB/s.
 struct WsChoice {
@@ -1092,7 +1167,7 @@ static WsChoice pick_ws(int M, int N, int K, bool swiglu, int max_split) {
     const int per = swiglu ? bn / 2 : bn;
     const int tiles_m = (M + bm - 1) / bm;
     const long tiles = (long)tiles_m * ((N + per - 1) / per);
-    const double per_k = c >= kFirstQuadTile ? (bm == 256 ? 1.5 : 1.17)
+    const double per_k = c >= kFirstQuadTile ? kQuadTileUs[c - kFirstQuadTile]
                                              : 1.9e-3 * bm + (tiles_m >= 2 ? 3.1e-3 : 4.2e-3) * bn;   // us per k-tile
     for (int ns = 1; ns <= max_split; ++ns) {
       const double rounds = (double)((tiles * ns + 255) / 256);
@@ -1290,6 +1365,7 @@ hipError_t launch_linear(int dtype, const LinearArgs& a, hipStream_t s, int forc
   }
   p.n_tiles = p.tiles_m * p.tiles_n * p.n_split;
   p.vec4 = a.N % 4 == 0 && ((reinterpret_cast<uintptr_t>(p.out) | reinterpret_cast<uintptr_t>(p.resid)) & 15) == 0;
+  p.vec8 = p.vec4 && a.N % 8 == 0;
   // Rotated k order for the two M-tiles of a W panel, when a block runs at
   // most 192 k-tiles.  Measured in the layers: LLaMA-13B preproj -13% and
   // ffn_ln1 -2%; LLaMA-33B at 288 rows every op -2..-5% (layer -4%); GPT-3

@@ -42,7 +42,7 @@ KINDS = [S.LINEAR_PLAIN, S.LINEAR_RESID, S.LINEAR_RESID_F32IN, S.LINEAR_SWIGLU, 
 
 @pytest.mark.parametrize("shift", [0, 1])
 @pytest.mark.parametrize("mnk", [(1, 4, 64), (255, 260, 128), (257, 515, 192), (193, 129, 448)])
-@pytest.mark.parametrize("tile", [(192, 256), (256, 256)])
+@pytest.mark.parametrize("tile", [(288, 192), (192, 256), (256, 256)])
 def test_quad_tile_edges(tile, mnk, shift):
     M, N, K = mnk
     index = [S.sarathi_linear_tile_shape(t) for t in range(S.sarathi_linear_tile_count())].index(tile)
