@@ -135,11 +135,24 @@ __global__ __launch_bounds__(256) void norm_kernel(const Tin* __restrict__ in, c
 
 // The first norm of a layer call with the metadata upload riding along:
 // block 0 copies the metadata chunk (as meta_write_kernel), blocks 1..rows
-// normalise rows 0..rows-1.  One launch instead of two.
+// normalise rows 0..rows-1.  One launch instead of two.  A fifth wave, when
+// launched, fills the row's part of the rotary table: once per row and call
+// instead of once per row, head and layer in the preproj epilogue.
 template <typename Tin, typename Tout, bool LAYER, int NC>
-__global__ __launch_bounds__(256) void norm_meta_kernel(const Tin* __restrict__ in, const Tout* __restrict__ g,
+__global__ __launch_bounds__(320) void norm_meta_kernel(const Tin* __restrict__ in, const Tout* __restrict__ g,
                                                         const Tout* __restrict__ b, Tout* __restrict__ out, int H,
-                                                        float eps, MetaChunk c, int* __restrict__ dst) {
+                                                        float eps, MetaChunk c, int* __restrict__ dst,
+                                                        RopeTable rope) {
+  if (threadIdx.x >= 256) {
+    const int i = threadIdx.x - 256, row = (int)blockIdx.x - 1;
+    if (row < 0 || i >= rope.hd / 2) return;
+    const int at = rope.pos_at + row;               // metadata past this chunk is already at dst
+    const int pos = at < META_CHUNK ? c.values[at] : dst[at];
+    float sn, cs;
+    rope_sincos(pos, rope_theta(i, rope.hd, log2((double)rope.base)), &sn, &cs);
+    rope.tab[row * rope.stride + i] = make_float2(cs, sn);
+    return;
+  }
   if (blockIdx.x == 0) {
     constexpr int PER = (META_CHUNK + 255) / 256;
     int v[PER];
@@ -157,10 +170,10 @@ __global__ __launch_bounds__(256) void norm_meta_kernel(const Tin* __restrict__ 
 
 template <typename Tin, typename Tout, bool LAYER, int NC>
 static void norm_launch_nc(const void* in, const void* g, const void* b, void* out, int rows, int H, float eps,
-                           hipStream_t s, const MetaChunk* meta, int* meta_dst) {
+                           hipStream_t s, const MetaChunk* meta, int* meta_dst, const RopeTable& rope) {
   if (meta)
-    hipLaunchKernelGGL((norm_meta_kernel<Tin, Tout, LAYER, NC>), dim3(rows + 1), dim3(256), 0, s, (const Tin*)in,
-                       (const Tout*)g, (const Tout*)b, (Tout*)out, H, eps, *meta, meta_dst);
+    hipLaunchKernelGGL((norm_meta_kernel<Tin, Tout, LAYER, NC>), dim3(rows + 1), dim3(rope.tab ? 320 : 256), 0, s,
+                       (const Tin*)in, (const Tout*)g, (const Tout*)b, (Tout*)out, H, eps, *meta, meta_dst, rope);
   else
     hipLaunchKernelGGL((norm_kernel<Tin, Tout, LAYER, NC>), dim3(rows), dim3(256), 0, s, (const Tin*)in,
                        (const Tout*)g, (const Tout*)b, (Tout*)out, H, eps);
@@ -168,35 +181,35 @@ static void norm_launch_nc(const void* in, const void* g, const void* b, void* o
 
 template <typename Tin, typename Tout, bool LAYER>
 static void norm_launch(const void* in, const void* g, const void* b, void* out, int rows, int H, float eps,
-                        hipStream_t s, const MetaChunk* meta, int* meta_dst) {
+                        hipStream_t s, const MetaChunk* meta, int* meta_dst, const RopeTable& rope) {
   constexpr int EI = Vec16<Tin>::N, EO = Vec16<Tout>::N;
   constexpr int CE = EI > EO ? EI : EO;
   const int nc = (H / CE + 255) / 256;
-  if (nc <= 2) norm_launch_nc<Tin, Tout, LAYER, 2>(in, g, b, out, rows, H, eps, s, meta, meta_dst);
-  else if (nc <= 4) norm_launch_nc<Tin, Tout, LAYER, 4>(in, g, b, out, rows, H, eps, s, meta, meta_dst);
-  else if (nc <= 6) norm_launch_nc<Tin, Tout, LAYER, 6>(in, g, b, out, rows, H, eps, s, meta, meta_dst);
-  else norm_launch_nc<Tin, Tout, LAYER, NORM_NC>(in, g, b, out, rows, H, eps, s, meta, meta_dst);
+  if (nc <= 2) norm_launch_nc<Tin, Tout, LAYER, 2>(in, g, b, out, rows, H, eps, s, meta, meta_dst, rope);
+  else if (nc <= 4) norm_launch_nc<Tin, Tout, LAYER, 4>(in, g, b, out, rows, H, eps, s, meta, meta_dst, rope);
+  else if (nc <= 6) norm_launch_nc<Tin, Tout, LAYER, 6>(in, g, b, out, rows, H, eps, s, meta, meta_dst, rope);
+  else norm_launch_nc<Tin, Tout, LAYER, NORM_NC>(in, g, b, out, rows, H, eps, s, meta, meta_dst, rope);
 }
 
 template <typename Tin, typename Tout>
 static void norm_dispatch(bool layer, const void* in, const void* g, const void* b, void* out, int rows, int H,
-                          float eps, hipStream_t s, const MetaChunk* meta, int* meta_dst) {
+                          float eps, hipStream_t s, const MetaChunk* meta, int* meta_dst, const RopeTable& rope) {
   if (layer)
-    norm_launch<Tin, Tout, true>(in, g, b, out, rows, H, eps, s, meta, meta_dst);
+    norm_launch<Tin, Tout, true>(in, g, b, out, rows, H, eps, s, meta, meta_dst, rope);
   else
-    norm_launch<Tin, Tout, false>(in, g, b, out, rows, H, eps, s, meta, meta_dst);
+    norm_launch<Tin, Tout, false>(in, g, b, out, rows, H, eps, s, meta, meta_dst, rope);
 }
 
 hipError_t launch_norm(int dtype, bool in_f32, bool layer_norm, const void* in, const void* g,
                        const void* b, void* out, int rows, int H, float eps, hipStream_t s,
-                       const MetaChunk* meta, int* meta_dst) {
+                       const MetaChunk* meta, int* meta_dst, RopeTable rope) {
   if (rows <= 0) return meta ? launch_meta_write(*meta, meta_dst, s) : hipSuccess;
   if (dtype == 0)
-    norm_dispatch<float, float>(layer_norm, in, g, b, out, rows, H, eps, s, meta, meta_dst);
+    norm_dispatch<float, float>(layer_norm, in, g, b, out, rows, H, eps, s, meta, meta_dst, rope);
   else if (in_f32)
-    norm_dispatch<float, bf16>(layer_norm, in, g, b, out, rows, H, eps, s, meta, meta_dst);
+    norm_dispatch<float, bf16>(layer_norm, in, g, b, out, rows, H, eps, s, meta, meta_dst, rope);
   else
-    norm_dispatch<bf16, bf16>(layer_norm, in, g, b, out, rows, H, eps, s, meta, meta_dst);
+    norm_dispatch<bf16, bf16>(layer_norm, in, g, b, out, rows, H, eps, s, meta, meta_dst, rope);
   return hipGetLastError();
 }
 

@@ -262,32 +262,27 @@ __device__ __forceinline__ int rope_w_row(int n, int N, int hd) {
 }
 
 // The epilogue: the block's tile goes to LDS as bf16 (the rounding the
-// separate kernel would read; 16-byte chunks XOR-swizzled by row), and behind
-// it the hd/2 frequencies, computed once per block in fp64 (every thread
-// computing its own eight took ~7 us of a 160-row block).  Each thread then
-// keeps one 16-column group (one head, 8 frequencies) and walks rows: q is
-// rotated into the output, k rotated and v copied into the KV cache at the
-// row's (slot, position), 16 bytes per access, both halves of the pairs
-// back at their physical columns.  The k and v columns of the output are not
-// written (attention reads them from the cache).
+// separate kernel would read; 16-byte chunks XOR-swizzled by row); each thread
+// then keeps one 16-column group (8 complete pairs of one head) and walks
+// rows, four at a time so that their loads share a round trip: q is rotated
+// into the output, k rotated and v copied into the KV cache at the row's
+// (slot, position), 16 bytes per access, both halves of the pairs back at
+// their physical columns.  The sines come from the call's rotary table.  The
+// k and v columns of the output are not written (attention reads them from
+// the cache).
 template <int BN>
 __device__ __forceinline__ int tile_chunk(int r, int c) {   // 16-byte chunk c of tile row r
   constexpr int MASK = (BN / 8) % 8 == 0 ? 7 : 3;          // the XOR stays within the row's chunks
   static_assert(BN / 8 % (MASK + 1) == 0, "chunks per row");
   return r * (BN / 8) + (c ^ (r & MASK));
 }
-template <int BM, int BN>
-__device__ __forceinline__ double* rope_thetas() {
-  extern __shared__ uint4 lds[];
-  return reinterpret_cast<double*>(lds + BM * BN / 8);
-}
-constexpr int ROPE_THETA_BYTES = 64 * 8;                  // head_dim up to 128
 
 template <int BM, int BN, int NT>
 __device__ __forceinline__ void rope_kv_walk(const GemmP& p, int m0, int n0, int tid) {
   extern __shared__ uint4 lds[];
   constexpr int JG = BN / 16;                               // 16-column groups per tile row
   constexpr int RS = NT / JG;                               // rows in flight
+  constexpr int U = 4;                                      // rows per round trip
   static_assert(RS > 0, "16-column groups");
   const int j = tid % JG, r0 = tid / JG;
   const int n = n0 + 16 * j;
@@ -297,41 +292,50 @@ __device__ __forceinline__ void rope_kv_walk(const GemmP& p, int m0, int n0, int
   const int part = n / QD, head = (n % QD) / hd;            // part 0 q, 1 k, 2 v
   const int d0 = (n % hd) / 2;                              // first pair of the group
   const bool rot = part < 2 && a.rope;
-  double theta[8];
-  if (rot) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) theta[e] = rope_thetas<BM, BN>()[d0 + e];
-  }
   bf16* cache = reinterpret_cast<bf16*>(a.kv_layer);
   const size_t kv_off = (part == 2 ? a.st.kv : 0) + (size_t)head * a.st.head;
-  for (int r = r0; r < BM; r += RS) {
-    const int row = m0 + r;
-    if (row >= p.M) break;
-    uint4 lo = lds[tile_chunk<BN>(r, 2 * j)];
-    uint4 hi = lds[tile_chunk<BN>(r, 2 * j + 1)];
-    const int slot = a.row_slot[row], pos = a.row_pos[row];
-    if (rot) {
-      float x0[8], x1[8];
-      Vec16<bf16>::unpack(lo, x0);
-      Vec16<bf16>::unpack(hi, x1);
-      uint32_t w0[4], w1[4];
+  const int rows = min(BM, p.M - m0);
+  for (int rb = r0; rb < rows; rb += U * RS) {
+    int slot[U], pos[U];
+    float4 cs[U][4];                                        // (cos, sin) of two pairs each
 #pragma unroll
-      for (int e = 0; e < 8; e += 2) {
-        float s0, c0, s1, c1;
-        rope_sincos(pos, theta[e], &s0, &c0);
-        rope_sincos(pos, theta[e + 1], &s1, &c1);
-        const bf16 a0 = f2bf(x0[e] * c0 - x1[e] * s0), b0 = f2bf(x0[e] * s0 + x1[e] * c0);
-        const bf16 a1 = f2bf(x0[e + 1] * c1 - x1[e + 1] * s1), b1 = f2bf(x0[e + 1] * s1 + x1[e + 1] * c1);
-        w0[e / 2] = (uint32_t)a0 | ((uint32_t)a1 << 16);
-        w1[e / 2] = (uint32_t)b0 | ((uint32_t)b1 << 16);
+    for (int u = 0; u < U; ++u) {
+      const int row = m0 + min(rb + u * RS, rows - 1);
+      slot[u] = a.row_slot[row];
+      pos[u] = a.row_pos[row];
+      if (rot) {
+        const float4* tab = reinterpret_cast<const float4*>(a.table + row * a.table_stride + d0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) cs[u][i] = tab[i];
       }
-      lo = make_uint4(w0[0], w0[1], w0[2], w0[3]);
-      hi = make_uint4(w1[0], w1[1], w1[2], w1[3]);
     }
-    bf16* dst = part == 0 ? reinterpret_cast<bf16*>(p.out) + (size_t)row * p.N + (n - n % hd)
-                          : cache + (size_t)slot * a.st.slot + kv_off + (size_t)pos * a.st.pos;
-    *reinterpret_cast<uint4*>(dst + d0) = lo;
-    *reinterpret_cast<uint4*>(dst + half + d0) = hi;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r = rb + u * RS;
+      if (r >= rows) break;
+      uint4 lo = lds[tile_chunk<BN>(r, 2 * j)];
+      uint4 hi = lds[tile_chunk<BN>(r, 2 * j + 1)];
+      if (rot) {
+        float x0[8], x1[8];
+        Vec16<bf16>::unpack(lo, x0);
+        Vec16<bf16>::unpack(hi, x1);
+        uint32_t w0[4], w1[4];
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+          const float c0 = cs[u][e / 2].x, s0 = cs[u][e / 2].y, c1 = cs[u][e / 2].z, s1 = cs[u][e / 2].w;
+          const bf16 a0 = f2bf(x0[e] * c0 - x1[e] * s0), b0 = f2bf(x0[e] * s0 + x1[e] * c0);
+          const bf16 a1 = f2bf(x0[e + 1] * c1 - x1[e + 1] * s1), b1 = f2bf(x0[e + 1] * s1 + x1[e + 1] * c1);
+          w0[e / 2] = (uint32_t)a0 | ((uint32_t)a1 << 16);
+          w1[e / 2] = (uint32_t)b0 | ((uint32_t)b1 << 16);
+        }
+        lo = make_uint4(w0[0], w0[1], w0[2], w0[3]);
+        hi = make_uint4(w1[0], w1[1], w1[2], w1[3]);
+      }
+      bf16* dst = part == 0 ? reinterpret_cast<bf16*>(p.out) + (size_t)(m0 + r) * p.N + (n - n % hd)
+                            : cache + (size_t)slot[u] * a.st.slot + kv_off + (size_t)pos[u] * a.st.pos;
+      *reinterpret_cast<uint4*>(dst + d0) = lo;
+      *reinterpret_cast<uint4*>(dst + half + d0) = hi;
+    }
   }
 }
 
@@ -359,7 +363,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
   static_assert(BM % 8 == 0 && BN % 8 == 0 && ILO > 0, "8-row groups");
   static_assert(WTM % 16 == 0 && WTN % 16 == 0 && (EPI != EPI_SWIGLU || FN % 2 == 0), "wave tile");
   static_assert((S - 2) * IHI < 64 && S >= 2, "stages");
-  static_assert(BM * BN * 2 + ROPE_THETA_BYTES <= S * ROWS * 128, "the RoPE epilogue stages the bf16 tile in the ring's LDS");
+  static_assert(BM * BN * 2 <= S * ROWS * 128, "the RoPE epilogue stages the bf16 tile in the ring's LDS");
   extern __shared__ uint4 lds[];                 // [S][ROWS * 8] 16-byte chunks
 
   const int per = gridDim.x / 8;
@@ -509,8 +513,6 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
           t16[tile_chunk<BN>(r, c >> 3) * 8 + (c & 7)] = f2bf(acc[fm][fn][i]);
         }
       }
-    if (p.rope.rope && tid < p.rope.hd / 2)
-      rope_thetas<BM, BN>()[tid] = rope_theta(tid, p.rope.hd, log2((double)p.rope.base));
     lds_read_barrier();                  // the producers pass their last barrier too
     rope_kv_walk<BM, BN, 64 * NC>(p, m0, tile_n * BN, tid);
     return;
@@ -851,8 +853,6 @@ __global__ __launch_bounds__(512, 2) void gemm_quad_kernel(GemmP p) {
                          (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16));
         }
       }
-    if (EPI == EPI_ROPE_KV && p.rope.rope && te < p.rope.hd / 2)
-      rope_thetas<BM, BN>()[te] = rope_theta(te, p.rope.hd, log2((double)p.rope.base));
     lds_read_barrier();
     if constexpr (EPI == EPI_ROPE_KV) {
       rope_kv_walk<BM, BN, 512>(p, m0, tile_n * BN, te);
@@ -1010,10 +1010,9 @@ static hipError_t run_ws(const GemmP& p, hipStream_t s) {
 
 template <int FM, int FN, int EPI>
 static hipError_t run_quad(const GemmP& p, hipStream_t s) {
-  // two stages of two halves, and room for the RoPE epilogue's frequencies
-  // behind its tile
+  // two stages of two halves (the RoPE epilogue's tile fits there)
   constexpr int ROWS0 = (2 * ((FM + 1) / 2) + 4 * ((FN + 1) / 2)) * 16;   // rows of a half stage
-  const size_t lds_bytes = (size_t)4 * ROWS0 * 128 + ROPE_THETA_BYTES;
+  const size_t lds_bytes = (size_t)4 * ROWS0 * 128;
   static std::atomic<uint64_t> lds_set{0};   // devices on which this instance's LDS limit is raised
   hipError_t e = ensure_dynamic_lds((const void*)gemm_quad_kernel<FM, FN, EPI>, (int)lds_bytes, lds_set);
   if (e != hipSuccess) return e;

@@ -22,12 +22,26 @@ struct MetaChunk {
 };
 hipError_t launch_meta_write(const MetaChunk& chunk, int* dst, hipStream_t s);
 
+// ---- rotary table of a call: row r's (cos, sin) of position pos_r at the hd/2
+// frequencies, fp32 pairs at tab + r * stride.  The first norm of a call fills
+// it; every layer's fused preproj epilogue reads it (all heads of q and k of a
+// row share the hd/2 pairs).  It lives in the k and v columns of the
+// workspace's qkv rows, which the fused preproj does not write.
+struct RopeTable {
+  float2* tab;          // null: none
+  size_t stride;        // float2 per row
+  int hd;
+  float base;
+  int pos_at;           // the rows' positions: metadata ints pos_at ..
+};
+
 // ---- norms (one row per block).  in: [rows, H] of Tin; out: [rows, H] of dtype.
 // With meta non-null the same launch also copies that metadata chunk to
-// meta_dst (one extra block).
+// meta_dst (one extra block), whose later chunks are already there, and fills
+// the rotary table (one more wave per row).
 hipError_t launch_norm(int dtype, bool in_f32, bool layer_norm, const void* in, const void* g,
                        const void* b, void* out, int rows, int H, float eps, hipStream_t s,
-                       const MetaChunk* meta = nullptr, int* meta_dst = nullptr);
+                       const MetaChunk* meta = nullptr, int* meta_dst = nullptr, RopeTable rope = RopeTable{});
 
 // ---- rotary embedding of q, k in place of the preproj output and K/V append.
 struct RopeArgs {
@@ -39,6 +53,8 @@ struct RopeArgs {
   const int* row_pos;   // [T]
   void* kv_layer;       // base of this layer's cache
   KVStrides st;
+  const float2* table;  // rotary table (fused preproj epilogue only)
+  size_t table_stride;
 };
 hipError_t launch_rope_append(int dtype, const RopeArgs& a, hipStream_t s);
 

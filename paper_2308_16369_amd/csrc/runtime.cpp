@@ -425,6 +425,11 @@ int layer_body(const Ctx& c, const sarathi_layer_weights* w, int layer, const vo
   float* hres = reinterpret_cast<float*>(ws + c.L.hres);
   float* parts = reinterpret_cast<float*>(ws + c.L.parts);
   const size_t parts_cap = (size_t)MAX_SPLIT * std::min(T, PARTS_ROWS) * H;
+  // the rotary table: hd/2 (cos, sin) pairs per row in the 2 QD bf16 columns
+  // behind a qkv row's q (written with the first layer's norm_1; no layer's
+  // fused preproj writes there)
+  float2* rope_tab = reinterpret_cast<float2*>(ws + c.L.qkv + (size_t)QD * 2);
+  const size_t rope_stride = (size_t)3 * QD * 2 / sizeof(float2);
   char* kv_layer = static_cast<char*>(c.kv->mem) + (size_t)layer * c.kv->st.layer * esize(cfg);
   hipError_t e;
   hipEvent_t* ev = prof_claim();
@@ -443,8 +448,10 @@ int layer_body(const Ctx& c, const sarathi_layer_weights* w, int layer, const vo
   } else if (carry_meta) {
     MetaChunk first;
     meta_chunk(P, 0, &first);
+    RopeTable rt{};
+    if (dt == SARATHI_BF16 && cfg->rope) rt = RopeTable{rope_tab, rope_stride, hd, cfg->rope_base, (int)P.o_pos};
     e = launch_norm(dt, false, ln, x_in, w->norm1_g, w->norm1_b, ws + c.L.a, T, H, cfg->eps, c.s, &first,
-                    reinterpret_cast<int*>(ws + c.L.meta));
+                    reinterpret_cast<int*>(ws + c.L.meta), rt);
   } else {
     e = launch_norm(dt, false, ln, x_in, w->norm1_g, w->norm1_b, ws + c.L.a, T, H, cfg->eps, c.s);
   }
@@ -456,6 +463,7 @@ int layer_body(const Ctx& c, const sarathi_layer_weights* w, int layer, const vo
   RopeArgs ra{};
   ra.qkv = ws + c.L.qkv; ra.T = T; ra.nh = nh; ra.hd = hd; ra.rope = cfg->rope; ra.base = cfg->rope_base;
   ra.row_slot = meta + P.o_slot; ra.row_pos = meta + P.o_pos; ra.kv_layer = kv_layer; ra.st = c.kv->st;
+  ra.table = rope_tab; ra.table_stride = rope_stride;
   bool rope_done = false;
   LinearArgs q{};
   q.kind = LIN_PLAIN; q.M = T; q.N = 3 * QD; q.K = H; q.x = ws + c.L.a; q.w = w->w_qkv; q.out = ws + c.L.qkv;
