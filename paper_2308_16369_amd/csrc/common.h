@@ -108,6 +108,12 @@ __device__ __forceinline__ void dma16(const void* src, uint4* dst) {
   __builtin_amdgcn_global_load_lds(src, (lds_void_t*)dst, 16, 0, 0);
 }
 
+// The same with the non-temporal hint (data read once: it does not allocate in
+// the memory-side cache).
+__device__ __forceinline__ void dma16_stream(const void* src, uint4* dst) {
+  __builtin_amdgcn_global_load_lds(src, (lds_void_t*)dst, 16, 0, 2);
+}
+
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt range");

@@ -34,6 +34,7 @@ struct GemmP {
                         // rotate their k-tile order
   void* out;            // [M, N]: dtype, or fp32 for EPI_RESID_TO_F32; EPI_PARTIAL: fp32 [n_split][M, N]
   const void* resid;    // EPI_RESID_TO_F32: dtype [M,N]; EPI_RESIDF32_TO_ACT: fp32 [M,N]
+  int stream_w;         // gemm_ws_kernel: W is read once (one M-tile) and loaded non-temporally
   int vec4, vec8;       // N a multiple of 4 / 8 and out, resid 16-byte aligned: wide stores
   RopeArgs rope;        // EPI_ROPE_KV: rotary embedding + KV append of the preproj output
 };
@@ -409,7 +410,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
     // HBM latency -- and found in L2 by the others a step later, instead of
     // all G waiting on the same miss.
     const int G = p.rotate_k ? p.tiles_m : 1, RD = p.rotate_k, GR = G * RD;
-    auto issue = [&](int stage, int kt) {
+    auto issue = [&](int stage, int kt, auto load) {
       if (G > 1) {
         const int base = kt / GR * GR;
         if (base + GR <= nk) kt = base + (kt - base + tile_m * RD) % GR;
@@ -423,26 +424,35 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
 #pragma unroll
       for (int j = IHI - 1; j >= 0; --j)
         if (j < ILO || extra)
-          dma16((min(j * NP + q, ROWS / 8 - 1) < GA ? a_k : w_k) + off[j] - back, dst + (j * NP + q) * 64);
+          load(min(j * NP + q, ROWS / 8 - 1) < GA, a_k + off[j] - back, w_k + off[j] - back, dst + (j * NP + q) * 64);
     };
     auto wait_next = [&](bool all) {   // all but the newest S - 2 stages landed
       if (all) wait_vmcnt<0>();
       else if (extra) wait_vmcnt<(S - 2) * IHI>();
       else wait_vmcnt<(S - 2) * ILO>();
     };
+    auto produce = [&](auto load) {
 #pragma unroll
-    for (int st = 0; st < S - 1; ++st)
-      if (st < nk) issue(st, st);
-    wait_next(S - 2 >= nk);
-    lds_barrier();
-    int nbuf = S - 1;
-    for (int kt = 0; kt < nk; ++kt) {
-      const bool more = kt + S - 1 < nk;
-      if (more) issue(nbuf, kt + S - 1);
-      wait_next(!more);
+      for (int st = 0; st < S - 1; ++st)
+        if (st < nk) issue(st, st, load);
+      wait_next(S - 2 >= nk);
       lds_barrier();
-      nbuf = (nbuf + 1 == S) ? 0 : nbuf + 1;
-    }
+      int nbuf = S - 1;
+      for (int kt = 0; kt < nk; ++kt) {
+        const bool more = kt + S - 1 < nk;
+        if (more) issue(nbuf, kt + S - 1, load);
+        wait_next(!more);
+        lds_barrier();
+        nbuf = (nbuf + 1 == S) ? 0 : nbuf + 1;
+      }
+    };
+    if (p.stream_w)
+      produce([](bool is_a, const char* a, const char* w, uint4* d) {
+        if (is_a) dma16(a, d);
+        else dma16_stream(w, d);
+      });
+    else
+      produce([](bool is_a, const char* a, const char* w, uint4* d) { dma16(is_a ? a : w, d); });
     if constexpr (EPI == EPI_ROPE_KV) lds_barrier();   // pairs with the consumers' epilogue barrier
     return;
   }
@@ -1075,9 +1085,9 @@ struct WsTile {
   int bm, bn;
 };
 constexpr WsTile kWsTiles[] = {{64, 64},   {64, 128},  {64, 256},  {96, 128},  {96, 192},  {96, 256},
-                               {160, 128}, {160, 192}, {160, 224}, {160, 256}, {288, 192}, {192, 256},
-                               {256, 256}};
-constexpr int kFirstQuadTile = 10;   // the rest run gemm_quad_kernel
+                               {128, 128}, {128, 192}, {128, 224}, {128, 256}, {160, 128}, {160, 192},
+                               {160, 224}, {160, 256}, {288, 192}, {192, 256}, {256, 256}};
+constexpr int kFirstQuadTile = 14;   // the rest run gemm_quad_kernel
 constexpr double kQuadTileUs[] = {1.27, 1.17, 1.5};   // their time per 64-wide k-tile
 constexpr int kNumWsTiles = sizeof(kWsTiles) / sizeof(kWsTiles[0]);
 
@@ -1090,12 +1100,16 @@ static hipError_t run_ws_cfg(int cfg, const GemmP& p, hipStream_t s) {
     case 3: return run_ws<bf16, 96, 128, 2, 4, 4, 5, EPI>(p, s);
     case 4: return run_ws<bf16, 96, 192, 2, 6, 4, 4, EPI>(p, s);
     case 5: return run_ws<bf16, 96, 256, 2, 4, 4, 3, EPI>(p, s);
-    case 6: return run_ws<bf16, 160, 128, 2, 4, 4, 4, EPI>(p, s);
-    case 7: return run_ws<bf16, 160, 192, 2, 6, 4, 3, EPI>(p, s);
-    case 8: return run_ws<bf16, 160, 224, 2, 7, 2, 3, EPI>(p, s);
-    case 9: return run_ws<bf16, 160, 256, 2, 4, 4, 3, EPI>(p, s);
-    case 10: return run_quad<9, 3, EPI>(p, s);
-    case 11: return run_quad<6, 4, EPI>(p, s);
+    case 6: return run_ws<bf16, 128, 128, 2, 4, 4, 4, EPI>(p, s);
+    case 7: return run_ws<bf16, 128, 192, 2, 6, 4, 3, EPI>(p, s);
+    case 8: return run_ws<bf16, 128, 224, 2, 7, 2, 3, EPI>(p, s);
+    case 9: return run_ws<bf16, 128, 256, 2, 4, 4, 3, EPI>(p, s);
+    case 10: return run_ws<bf16, 160, 128, 2, 4, 4, 4, EPI>(p, s);
+    case 11: return run_ws<bf16, 160, 192, 2, 6, 4, 3, EPI>(p, s);
+    case 12: return run_ws<bf16, 160, 224, 2, 7, 2, 3, EPI>(p, s);
+    case 13: return run_ws<bf16, 160, 256, 2, 4, 4, 3, EPI>(p, s);
+    case 14: return run_quad<9, 3, EPI>(p, s);
+    case 15: return run_quad<6, 4, EPI>(p, s);
     default: return run_quad<8, 4, EPI>(p, s);
   }
 }
@@ -1156,12 +1170,17 @@ struct WsChoice {
   int cfg, n_split;
 };
 static WsChoice pick_ws(int M, int N, int K, bool swiglu, int max_split) {
-  WsChoice best{6, 1};
+  WsChoice best{10, 1};
   double best_t = 1e300;
   const int nk = K / 64;
   for (int c = 0; c < kNumWsTiles; ++c) {
     const int bm = kWsTiles[c].bm, bn = kWsTiles[c].bn;
-    if (bm == 64 && M > 64) continue;    // 64-row tiles only for short batches
+    if (bm == 64 && M > 128) continue;   // 64-row tiles only for short batches
+    // 128-row tiles: two cover 256 rows where 160-row ones pad to 320 (LLaMA-13B
+    // at 256 rows, alone: preproj 55.7 -> 52.4 us, ffn_ln1 84.2 -> 77.2, ffn_ln2
+    // 51.0 -> 49.2).  K below 1024 keeps the picks that the tile tests pin
+    // (200 x 19968 x 512 would gain 1.2 of 13.4 us).
+    if (bm == 128 && (M <= 96 || K < 1024)) continue;
     if (c >= kFirstQuadTile && M <= 160) continue;
     const int per = swiglu ? bn / 2 : bn;
     const int tiles_m = (M + bm - 1) / bm;
@@ -1365,6 +1384,12 @@ hipError_t launch_linear(int dtype, const LinearArgs& a, hipStream_t s, int forc
   p.n_tiles = p.tiles_m * p.tiles_n * p.n_split;
   p.vec4 = a.N % 4 == 0 && ((reinterpret_cast<uintptr_t>(p.out) | reinterpret_cast<uintptr_t>(p.resid)) & 15) == 0;
   p.vec8 = p.vec4 && a.N % 8 == 0;
+  // One M-tile: every W line is read once, so it is loaded non-temporally
+  // (alone, weights from HBM: LLaMA-13B 4 rows ffn_ln1 49.5 -> 44.4 us, 5.7 ->
+  // 6.4 TB/s; LLaMA-33B 160 rows ffn_ln1 107 -> 97; GPT-3 30 rows ffn_ln2 215 ->
+  // 189; the quadrant tiles gain nothing).  Not below 32 MB: the weights of such a model can stay in the 256 MB
+  // memory-side cache from call to call.  Two M-tiles meet in L2 instead.
+  p.stream_w = ws && cfg < kFirstQuadTile && p.tiles_m == 1 && w_rows * a.K * 2 >= (32u << 20);
   // Rotated k order for the two M-tiles of a W panel, when a block runs at
   // most 192 k-tiles.  Measured in the layers: LLaMA-13B preproj -13% and
   // ffn_ln1 -2%; LLaMA-33B at 288 rows every op -2..-5% (layer -4%); GPT-3
