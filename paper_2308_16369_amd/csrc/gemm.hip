@@ -467,47 +467,78 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
 
   lds_barrier();
   int buf = 0;
-  for (int kt = 0; kt < nk; ++kt) {
-    const uint4* s = lds + buf * ROWS * 8;
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const int ch = ks * 4 + (lane >> 4);
-      using Frag = std::conditional_t<F32, floatx4, bf16x8_t>;
-      Frag af[FM], bfr[FN];
+  if constexpr (F32) {
+    // The fragments of the other half k-tile are read while this one's
+    // products run (one consumer wave per SIMD: nothing else hides the reads).
+    floatx4 af[2][FM], bfr[2][FN];
+    auto read = [&](auto h, int at, int kt) {
+      constexpr int HF = decltype(h)::value;
+      const uint4* s = lds + at * ROWS * 8;
+      const int ch = HF * 4 + (lane >> 4);
 #pragma unroll
       for (int fm = 0; fm < FM; ++fm) {
         const int r = wm * WTM + fm * 16 + (lane & 15);
-        af[fm] = __builtin_bit_cast(Frag, s[r * 8 + (ch ^ (r & 7))]);
+        af[HF][fm] = __builtin_bit_cast(floatx4, s[r * 8 + (ch ^ (r & 7))]);
       }
 #pragma unroll
       for (int fn = 0; fn < FN; ++fn) {
         const int r = BM + wn * WTN + fn * 16 + (lane & 15);
-        bfr[fn] = __builtin_bit_cast(Frag, s[r * 8 + (ch ^ (r & 7))]);
+        bfr[HF][fn] = __builtin_bit_cast(floatx4, s[r * 8 + (ch ^ (r & 7))]);
       }
-      if constexpr (F32) {
-        if (kbeg + (kt + 1) * BK > kend && kbeg + kt * BK + ch * 4 >= kend) {   // chunks past K: both operands zero
+      if (kbeg + (kt + 1) * BK > kend && kbeg + kt * BK + ch * 4 >= kend) {   // chunks past K: both operands zero
 #pragma unroll
-          for (int fm = 0; fm < FM; ++fm) af[fm] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int fm = 0; fm < FM; ++fm) af[HF][fm] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int fn = 0; fn < FN; ++fn) bfr[fn] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int fn = 0; fn < FN; ++fn) bfr[HF][fn] = floatx4{0.f, 0.f, 0.f, 0.f};
+      }
+    };
+    auto products = [&](auto h) {
+      constexpr int HF = decltype(h)::value;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+          for (int fn = 0; fn < FN; ++fn)
+            acc[fm][fn] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[HF][fm][j], bfr[HF][fn][j], acc[fm][fn], 0, 0, 0);
+    };
+    using H0 = std::integral_constant<int, 0>;
+    using H1 = std::integral_constant<int, 1>;
+    read(H0{}, 0, 0);
+    for (int kt = 0; kt < nk; ++kt) {
+      read(H1{}, buf, kt);
+      products(H0{});
+      lds_read_barrier();
+      buf = (buf + 1 == S) ? 0 : buf + 1;
+      if (kt + 1 < nk) read(H0{}, buf, kt + 1);
+      products(H1{});
+    }
+  } else {
+    for (int kt = 0; kt < nk; ++kt) {
+      const uint4* s = lds + buf * ROWS * 8;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const int ch = ks * 4 + (lane >> 4);
+        bf16x8_t af[FM], bfr[FN];
+#pragma unroll
+        for (int fm = 0; fm < FM; ++fm) {
+          const int r = wm * WTM + fm * 16 + (lane & 15);
+          af[fm] = __builtin_bit_cast(bf16x8_t, s[r * 8 + (ch ^ (r & 7))]);
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int fm = 0; fm < FM; ++fm)
-#pragma unroll
-            for (int fn = 0; fn < FN; ++fn)
-              acc[fm][fn] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[fm][j], bfr[fn][j], acc[fm][fn], 0, 0, 0);
-      } else {
+        for (int fn = 0; fn < FN; ++fn) {
+          const int r = BM + wn * WTN + fn * 16 + (lane & 15);
+          bfr[fn] = __builtin_bit_cast(bf16x8_t, s[r * 8 + (ch ^ (r & 7))]);
+        }
 #pragma unroll
         for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
           for (int fn = 0; fn < FN; ++fn)
             acc[fm][fn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[fm], bfr[fn], acc[fm][fn], 0, 0, 0);
       }
+      lds_read_barrier();
+      buf = (buf + 1 == S) ? 0 : buf + 1;
     }
-    lds_read_barrier();
-    buf = (buf + 1 == S) ? 0 : buf + 1;
   }
 
   if constexpr (EPI == EPI_ROPE_KV) {
