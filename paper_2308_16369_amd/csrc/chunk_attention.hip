@@ -515,6 +515,194 @@ __global__ __launch_bounds__(64 * NW) void attn_prefill_bf16_kernel(PrefillArgs 
   }
 }
 
+// ============================================================================ prefill (fp32, MFMA)
+// The same work items for fp32: a block of 4 waves x 16 queries, one head, one
+// range of keys, in tiles of 32 keys.  Reading each key once per row instead
+// (row attention on the chunk rows) took 235 us of a LLaMA-13B-wide layer of
+// 128 chunk rows and 16 decodes; here a key tile serves 64 rows.
+//   S^T = K Q^T on v_mfma_f32_16x16x4_f32: a lane's four consecutive k of a
+//     16-wide step are one 16-byte read, product j takes element j of every
+//     lane.  Lane l then holds the scores of query l % 16 for keys 4 (l/16) + i
+//     of each 16-key block, which is the B operand of
+//   O^T += V^T P^T: product j sums keys {j, 4 + j, 8 + j, 12 + j}; its A
+//     operand is V[4 (l/16) + j][16 db + l % 16], one word per lane.
+// K and V go through registers into padded LDS rows (D + 4 floats: both reads
+// are conflict-free), two stages, the next tile's loads in flight during this
+// one's products.  Bound by the fp32 matrix rate: 128 products of 32 cycles per
+// wave and tile (D = 128), with one or two waves per SIMD.
+template <int D>
+__global__ __launch_bounds__(256) void attn_prefill_f32_kernel(PrefillArgs a, float scale_log2) {
+  constexpr int QB = PREFILL_QBLOCK_F32, KT = 32, LD = D + 4;
+  constexpr int NL = KT * D / 4 / 256;   // 16-byte loads per thread per K (or V) tile
+  static_assert(NL * 256 * 4 == KT * D, "tile loads");
+  extern __shared__ u32x4 ring[];        // [2] stages of K rows, then V rows
+  float* smem = reinterpret_cast<float*>(ring);
+
+  const int per = gridDim.x / 8;
+  const int t = (blockIdx.x % 8) * per + blockIdx.x / 8;
+  if (t >= a.n_work * a.nh) return;
+  const int item = t % a.n_work, h = t / a.n_work;
+  const int* wk = a.work + 4 * item;
+  const int* ch = a.chunks + 4 * wk[0];
+  const int slot = ch[0], offset = ch[1], C = ch[2], row0 = ch[3];
+  const int q0 = wk[1] * QB, pslot = wk[2];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int g = lane >> 4, ql = lane & 15;
+  const float* qkv = reinterpret_cast<const float*>(a.qkv) + (size_t)row0 * a.ld_qkv;
+  const float* kbase = reinterpret_cast<const float*>(a.kv_layer) + (size_t)slot * a.st.slot + (size_t)h * a.st.head;
+  const float* vbase = kbase + a.st.kv;
+
+  const int n_keys = offset + min(q0 + QB, C);
+  const int kbeg = (wk[3] >> 16) * 64;
+  const int kend = min(n_keys, (wk[3] & 0xffff) * 64);
+  const int n_tiles = (kend - kbeg + KT - 1) / KT;
+
+  const int wq0 = q0 + wave * 16, myq = wq0 + ql;
+  const int qpos = offset + myq, last_key = offset + wq0 + 15;
+  floatx4 qf[D / 16];                    // query ql, k = 16 s + 4 g + i
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s) {
+    const floatx4 v = *reinterpret_cast<const floatx4*>(qkv + (size_t)min(myq, C - 1) * a.ld_qkv + h * D + 16 * s + 4 * g);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) qf[s][i] = myq < C ? v[i] * scale_log2 : 0.f;
+  }
+  float m_run = -INFINITY, l_run = 0.f;  // l_run: this lane's keys
+  floatx4 o_acc[D / 16];                 // O^T[d = 16 db + 4 g + i][q = ql]
+#pragma unroll
+  for (int db = 0; db < D / 16; ++db) o_acc[db] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  floatx4 kr[NL], vr[NL];
+  auto load = [&](int kt) {              // keys past the item's end re-read its last key (masked)
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int e = i * 256 + tid, row = e / (D / 4), c = e % (D / 4);
+      const size_t at = (size_t)min(kbeg + kt * KT + row, kend - 1) * a.st.pos + 4 * c;
+      kr[i] = *reinterpret_cast<const floatx4*>(kbase + at);
+      vr[i] = *reinterpret_cast<const floatx4*>(vbase + at);
+    }
+  };
+  // A tile with masked keys multiplies their V by a probability of 0: should V
+  // hold an infinity or NaN there (a later row's own), the rows before it must
+  // not see it.  Such a tile (the stores look for it) takes the products one
+  // key at a time, unmasked keys only.
+  auto store = [&](int kt) -> int {      // nonzero: this thread stored a non-finite V of a tile with masked keys
+    float* ks = smem + (kt & 1) * 2 * KT * LD;
+    int bad = 0;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int e = i * 256 + tid, row = e / (D / 4), c = e % (D / 4);
+      *reinterpret_cast<floatx4*>(ks + row * LD + 4 * c) = kr[i];
+      *reinterpret_cast<floatx4*>(ks + (KT + row) * LD + 4 * c) = vr[i];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) bad |= !(fabsf(vr[i][x]) < INFINITY);
+    }
+    const int end = kbeg + (kt + 1) * KT;
+    return end > kend || end - 1 > offset + q0 ? bad : 0;
+  };
+  load(0);
+  int by_key = __syncthreads_or(store(0));
+  for (int kt = 0; kt < n_tiles; ++kt) {
+    if (kt + 1 < n_tiles) load(kt + 1);
+    const int k0 = kbeg + kt * KT;
+    if (k0 <= last_key) {                // else every key lies past the wave's last query
+      const float* ks = smem + (kt & 1) * 2 * KT * LD;
+      const float* vs = ks + KT * LD;
+      floatx4 s[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+      for (int st = 0; st < D / 16; ++st) {
+        floatx4 kf[2];
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+          kf[kb] = *reinterpret_cast<const floatx4*>(ks + (kb * 16 + ql) * LD + 16 * st + 4 * g);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int kb = 0; kb < 2; ++kb)
+            s[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kb][j], qf[st][j], s[kb], 0, 0, 0);
+      }
+      const int lim = min(qpos, kend - 1) - k0;   // the lane's last unmasked key, tile-relative
+      float mx = -INFINITY;
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (kb * 16 + 4 * g + i > lim) s[kb][i] = -INFINITY;
+          mx = fmaxf(mx, s[kb][i]);
+        }
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float m_new = fmaxf(m_run, mx);
+      const float m_use = m_new == -INFINITY ? 0.f : m_new;   // no key of this query so far
+      const float corr = exp2f(m_run - m_use);
+      m_run = m_new;
+      l_run *= corr;
+#pragma unroll
+      for (int db = 0; db < D / 16; ++db) o_acc[db] *= corr;
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          s[kb][i] = exp2f(s[kb][i] - m_use);
+          l_run += s[kb][i];
+        }
+      if (!by_key) {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int db = 0; db < D / 16; ++db)
+              o_acc[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(vs[(kb * 16 + 4 * g + j) * LD + 16 * db + ql], s[kb][j],
+                                                               o_acc[db], 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            for (int gk = 0; gk < 4; ++gk) {
+              const int key = kb * 16 + 4 * gk + i;
+              const float w = __shfl(s[kb][i], gk * 16 + ql, 64);
+              if (key > lim) continue;
+#pragma unroll
+              for (int db = 0; db < D / 16; ++db)
+#pragma unroll
+                for (int x = 0; x < 4; ++x) o_acc[db][x] = fmaf(w, vs[key * LD + 16 * db + 4 * g + x], o_acc[db][x]);
+            }
+      }
+    }
+    // the next tile's stage: its last readers passed the barrier before this tile
+    by_key = __syncthreads_or(kt + 1 < n_tiles ? store(kt + 1) : 0);
+  }
+  l_run += __shfl_xor(l_run, 16, 64);
+  l_run += __shfl_xor(l_run, 32, 64);
+
+  if (myq >= C) return;
+  if (pslot < 0) {                       // every key of the row: normalised O
+    const float inv = 1.0f / l_run;
+    float* out = reinterpret_cast<float*>(a.out) + (size_t)(row0 + myq) * a.ld_out + h * D + 4 * g;
+#pragma unroll
+    for (int db = 0; db < D / 16; ++db) *reinterpret_cast<floatx4*>(out + 16 * db) = o_acc[db] * inv;
+    return;
+  }
+  float* prow = a.part + ((size_t)(pslot * QB + wave * 16 + ql) * a.nh + h) * (D + PART_O);
+  if (g == 0) {
+    prow[0] = m_run;
+    prow[1] = l_run;
+  }
+#pragma unroll
+  for (int db = 0; db < D / 16; ++db) *reinterpret_cast<floatx4*>(prow + PART_O + 16 * db + 4 * g) = o_acc[db];
+}
+
+template <int D>
+static hipError_t run_prefill_f32(const PrefillArgs& a, unsigned grid, float scale_log2, hipStream_t s) {
+  const size_t lds_bytes = (size_t)2 * 2 * 32 * (D + 4) * 4;   // two stages of 32 K + 32 V rows
+  static std::atomic<uint64_t> lds_set{0};   // devices on which this instance's LDS limit is raised
+  hipError_t e = ensure_dynamic_lds((const void*)attn_prefill_f32_kernel<D>, (int)lds_bytes, lds_set);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((attn_prefill_f32_kernel<D>), dim3(grid), dim3(256), lds_bytes, s, a, scale_log2);
+  return hipGetLastError();
+}
+
 template <int D, int NW, int R>
 static hipError_t run_prefill(const PrefillArgs& a, unsigned grid, float scale_log2, hipStream_t s) {
   const size_t lds_bytes = (size_t)2 * R * 64 * (D / 8) * 16;   // R K + R V tile stages
@@ -527,9 +715,12 @@ static hipError_t run_prefill(const PrefillArgs& a, unsigned grid, float scale_l
 
 hipError_t launch_attn_prefill(int dtype, const PrefillArgs& a, hipStream_t s) {
   if (a.n_work <= 0) return hipSuccess;
-  if (dtype != 1) return hipErrorInvalidValue;
   const float scale_log2 = LOG2E / sqrtf((float)a.hd);
   const unsigned grid = (unsigned)(((size_t)a.n_work * a.nh + 7) / 8 * 8);
+  if (dtype == 0) {
+    if (a.qblock != PREFILL_QBLOCK_F32) return hipErrorInvalidValue;
+    return a.hd == 128 ? run_prefill_f32<128>(a, grid, scale_log2, s) : run_prefill_f32<64>(a, grid, scale_log2, s);
+  }
   // 256-row q-blocks: 8 waves, 4-deep K and V rings (128 KB for head_dim 128,
   // one block per CU); 128-row q-blocks: 4 waves, 3-deep rings (96 KB)
   if (a.qblock == PREFILL_QBLOCK_SMALL) {

@@ -3,7 +3,7 @@
 // unnormalised o) that the combine pass of attention_combine.hip merges per
 // row.
 //
-// Row attention (decodes; in fp32 runs also the chunk rows): each row attends
+// Row attention (the decodes): each row attends
 // to keys 0..pos of its slot.  Work item = (row, split of split_keys keys); a
 // block of 4 (fp32) or 8 (bf16) waves streams its split, each wave 32 keys per
 // pass with 16-byte non-temporal loads (a key row spread over hd*size/16
@@ -42,7 +42,7 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(RowAttnArgs a, float sca
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane / LPK, j = lane % LPK;
   const int wv = a.work[item];
-  const int row_rel = wv >> 12, split = wv & 4095;
+  const int row_rel = wv >> 12, split = wv & (ROW_DIRECT - 1);
   const int row = a.row_base + row_rel;
   const int slot = a.row_slot[row];
   const int nk = a.row_pos[row] + 1;
@@ -146,6 +146,21 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(RowAttnArgs a, float sca
   __syncthreads();
   float M = fmaxf(fmaxf(red_m[0], red_m[1]), fmaxf(red_m[2], red_m[3]));
   const float Ms = (M == -INFINITY) ? 0.f : M;
+  if (wv & ROW_DIRECT) {
+    // the row's only split: normalised here as the combine pass would
+    float L = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) L += red_l[w] * exp2f(red_m[w] - Ms);
+    const float inv = 1.0f / L;
+    T* out = reinterpret_cast<T*>(a.out) + (size_t)row * a.ld_out + h * D;
+    for (int d = tid; d < D; d += 256) {
+      float acc = 0.f;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) acc += red_o[w][d] * exp2f(red_m[w] - Ms);
+      out[d] = from_f<T>(acc * inv);
+    }
+    return;
+  }
   float* dst = a.part + ((size_t)(a.part_base + item) * a.nh + h) * (D + PART_O);
   for (int d = tid; d < D; d += 256) {
     float acc = 0.f;

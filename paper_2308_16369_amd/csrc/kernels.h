@@ -119,6 +119,7 @@ constexpr int PART_O = 4;
 // picks one per batch.  Buffers are sized for the larger.
 constexpr int PREFILL_QBLOCK = 256;
 constexpr int PREFILL_QBLOCK_SMALL = 128;
+constexpr int PREFILL_QBLOCK_F32 = 64;      // fp32: 4 waves x 16 queries
 struct PrefillArgs {
   const void* qkv;      // all rows; chunk c's rows start at its first-row entry; q columns rotated
   int ld_qkv;
@@ -128,7 +129,7 @@ struct PrefillArgs {
   int nh, hd;
   const int* work;      // [n_work][chunk, q_block, partial slot p, (first key tile << 16) | end key tile]
   int n_work;
-  int qblock;           // rows per q-block: PREFILL_QBLOCK or PREFILL_QBLOCK_SMALL
+  int qblock;           // rows per q-block: PREFILL_QBLOCK or PREFILL_QBLOCK_SMALL (bf16), PREFILL_QBLOCK_F32
   float* part;          // row j of an item's q-block -> partial index p * qblock + j
   void* out;            // p < 0 (the item covers every key of its rows): normalised rows of O [T, nh*hd]
   int ld_out;
@@ -144,11 +145,14 @@ struct RowAttnArgs {
   KVStrides st;
   const int* row_slot;
   const int* row_pos;
-  const int* work;      // [n_work] (row_rel << 12) | split
+  const int* work;      // [n_work] (row_rel << 12) | split (| ROW_DIRECT: fp32, the row's only split)
   int row_base, n_work, split_keys, nh, hd;
   float* part;          // work item w -> partial index part_base + w
   int part_base;
+  void* out;            // ROW_DIRECT items: the row of O [T, nh*hd], no partial
+  int ld_out;
 };
+constexpr int ROW_DIRECT = 1 << 11;   // positions < 2^20 make at most 2048 splits
 hipError_t launch_attn_rows(int dtype, const RowAttnArgs& a, hipStream_t s);
 
 // Combine: row r's partials are comb[3r] + j * comb[3r + 2] for j < comb[3r + 1];

@@ -106,7 +106,9 @@ Layout make_layout(const sarathi_model_cfg* c, int T, int n_chunks, int S) {
   L.m = take(T * F * es);
   L.parts = take((size_t)MAX_SPLIT * std::min(T, PARTS_ROWS) * H * 4);
   // query blocks of QBLOCK rows (each chunk starts a new block), at most one
-  // key range per PRE_SPLIT keys each
+  // key range per PRE_SPLIT keys each.  (fp32 blocks of 64 rows: fewer partial
+  // rows; their work items, up to four times as many, are 1/8 of the list
+  // entries that max_dec holds for the chunk's rows, and four per chunk more.)
   const size_t max_pre = ((size_t)(T + QBLOCK - 1) / QBLOCK + n_chunks - 1) * ((S + PRE_SPLIT - 1) / PRE_SPLIT);
   const size_t max_dec = (size_t)T * ((S + SPLIT_KEYS - 1) / SPLIT_KEYS);
   L.part = take((max_pre * QBLOCK + max_dec) * c->n_heads * (c->head_dim + PART_O) * 4);
@@ -166,7 +168,7 @@ int from_mixed(const sarathi_mixed_batch* b, BatchDesc* out) {
 // Host-side description of the batch and its device metadata.
 struct Plan {
   int C, B, T, row_base, n_pre, n_dec, n_chunks, pre_tiles;
-  int qblock;      // chunk rows per chunk-attention q-block (PREFILL_QBLOCK or PREFILL_QBLOCK_SMALL)
+  int qblock;      // chunk rows per chunk-attention q-block (PREFILL_QBLOCK, _SMALL or _F32)
   int pre_slots;   // partial q-block slots of the chunk items (items covering all keys of their rows write O)
   int comb_row0;   // first row whose attention output the combine pass writes
   // row_slot[T] row_pos[T] comb[3T] chunk table [n_chunks][slot, offset, len, first row]
@@ -213,11 +215,11 @@ Plan make_plan(const sarathi_model_cfg* cfg, const BatchDesc& b) {
   p.C = b.rows() - b.B;
   p.T = p.C + p.B;
   p.n_chunks = (int)b.chunks.size();
-  // bf16: chunk rows go to the MFMA chunk-attention kernel (work item = one
-  // chunk's query block x key split), decodes to row attention (work
-  // item = row x key split).  fp32: every row goes to row attention (a chunk
-  // row at position p is attention over keys 0..p, like a decode with ctx = p).
-  p.row_base = (cfg->dtype == SARATHI_BF16) ? p.C : 0;
+  // chunk rows go to the chunk-attention kernel (work item = one chunk's query
+  // block x key split), decodes to row attention (work item = row x key split).
+  // fp32 chunk rows may go to row attention too (below).
+  const bool f32 = cfg->dtype == SARATHI_F32;
+  p.row_base = p.C;
   p.pre_tiles = PRE_SPLIT / 64;
   p.qblock = QBLOCK;
   p.pre_slots = 0;
@@ -229,6 +231,8 @@ Plan make_plan(const sarathi_model_cfg* cfg, const BatchDesc& b) {
     r0 += c.len;
   }
   for (int i = 0; i < p.B; ++i) { slot[p.C + i] = b.dslots[i]; pos[p.C + i] = b.dctx[i]; }
+  std::vector<int> qtiles;   // tiles of every q-block, chunk by chunk
+  int tau = PRE_SPLIT / 64;
   if (p.row_base > 0) {
     // Partial slots run q-block by q-block (a row's splits are consecutive,
     // qblock partial rows apart); the work items run split by split so that
@@ -244,11 +248,12 @@ Plan make_plan(const sarathi_model_cfg* cfg, const BatchDesc& b) {
     // (measured on the LLaMA-13B, LLaMA-33B and GPT-3 chunk shapes), and
     // wins when the chunk is short or the heads few (fewer idle waves and a
     // smaller set-up and output per block).
-    std::vector<int> qtiles;   // tiles of every q-block, chunk by chunk
-    int tau = PRE_SPLIT / 64;
     double best = 1e300;
     p.qblock = QBLOCK;
-    for (const int qbs : {QBLOCK, PREFILL_QBLOCK_SMALL}) {
+    // fp32 has one block size (64 rows)
+    const std::vector<int> sizes =
+        f32 ? std::vector<int>{PREFILL_QBLOCK_F32} : std::vector<int>{QBLOCK, PREFILL_QBLOCK_SMALL};
+    for (const int qbs : sizes) {
       const double per_tile = qbs == QBLOCK ? 1.0 : 0.82;
       std::vector<int> qt;
       int t_max = 1;
@@ -277,6 +282,21 @@ Plan make_plan(const sarathi_model_cfg* cfg, const BatchDesc& b) {
         }
       }
     }
+    if (f32) {
+      // A few rows of a few heads are as well taken one by one, each a block
+      // (a chunk row at position p is a decode with ctx = p): row attention
+      // reads ~7.2 TB/s out of L2 beside ~4 us of launch and latency; the chunk
+      // kernel takes 5 us (head_dim 64) or 9 (128) per 64-key tile of its
+      // longest block.  64 rows x 4 heads at 128: 7.7 against 16.5 us; 128 rows
+      // x 40 heads at 256: 164 (of 235 with 16 decodes) against 27.
+      double bytes = 0;
+      for (const ChunkDesc& c : b.chunks) bytes += c.len * (c.offset + 0.5 * (c.len + 1));
+      bytes *= (double)cfg->n_heads * cfg->head_dim * 2 * 4;
+      // best = rounds x (longest + 4 tiles) of the block model
+      if (bytes / 7.2e6 + 4.0 < best * (1.0 + 0.0625 * cfg->head_dim) * 0.6) p.row_base = 0;
+    }
+  }
+  if (p.row_base > 0) {
     p.pre_tiles = tau;
     r0 = 0;
     int slot_base = 0, qi = 0;
@@ -319,10 +339,13 @@ Plan make_plan(const sarathi_model_cfg* cfg, const BatchDesc& b) {
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return slot[x] < slot[y]; });
   for (int r : order) {
     const int ns = (pos[r] + 1 + SPLIT_KEYS - 1) / SPLIT_KEYS;
+    // fp32: a row of one split is written by its attention block (no combine;
+    // a batch of such rows saves the pass: 3 us of the tiny layer's 47)
+    const bool direct = f32 && ns == 1;
     comb[3 * r] = pre_rows + (int)dec.size();
-    comb[3 * r + 1] = ns;
+    comb[3 * r + 1] = direct ? 0 : ns;
     comb[3 * r + 2] = 1;
-    for (int s = 0; s < ns; ++s) dec.push_back(((r - p.row_base) << 12) | s);
+    for (int s = 0; s < ns; ++s) dec.push_back(((r - p.row_base) << 12) | (direct ? ROW_DIRECT : 0) | s);
   }
   p.n_pre = (int)pre.size() / 4;
   p.n_dec = (int)dec.size();
@@ -497,6 +520,7 @@ int layer_body(const Ctx& c, const sarathi_layer_weights* w, int layer, const vo
     da.row_slot = meta + P.o_slot; da.row_pos = meta + P.o_pos; da.work = meta + P.o_dec;
     da.row_base = P.row_base; da.n_work = P.n_dec; da.split_keys = SPLIT_KEYS; da.nh = nh; da.hd = hd;
     da.part = part; da.part_base = P.pre_slots * P.qblock;
+    da.out = ws + c.L.o; da.ld_out = QD;
     e = launch_attn_rows(dt, da, c.s);
     if (e != hipSuccess) return hip_fail(e, "decode attention");
   }
@@ -858,6 +882,7 @@ int sarathi_attention_plan(const sarathi_model_cfg* cfg, const sarathi_hybrid_ba
   o.chunk_items = P.n_pre;
   o.decode_items = P.n_dec;
   long written = P.n_dec;
+  for (int i = 0; i < P.n_dec; ++i) written -= (P.meta[P.o_dec + i] & ROW_DIRECT) != 0;
   for (int i = 0; i < P.n_pre; ++i)
     if (pre[4 * i + 2] >= 0) {
       const int len = chunks[4 * pre[4 * i] + 2], q0 = pre[4 * i + 1] * P.qblock;
