@@ -262,8 +262,8 @@ __device__ __forceinline__ int rope_w_row(int n, int N, int hd) {
   return n - c + ((c >> 3) & 1) * (hd / 2) + (c >> 4) * 8 + (c & 7);
 }
 
-// The epilogue: the block's tile goes to LDS as bf16 (the rounding the
-// separate kernel would read; 16-byte chunks XOR-swizzled by row); each thread
+// The epilogue: the block's tile goes to LDS in the output type (the rounding
+// the separate kernel would read; 16-byte chunks XOR-swizzled by row); each thread
 // then keeps one 16-column group (8 complete pairs of one head) and walks
 // rows, four at a time so that their loads share a round trip: q is rotated
 // into the output, k rotated and v copied into the KV cache at the row's
@@ -271,14 +271,28 @@ __device__ __forceinline__ int rope_w_row(int n, int N, int hd) {
 // their physical columns.  The sines come from the call's rotary table.  The
 // k and v columns of the output are not written (attention reads them from
 // the cache).
-template <int BN>
+template <int BN, int E = 8>                                // E elements per 16-byte chunk
 __device__ __forceinline__ int tile_chunk(int r, int c) {   // 16-byte chunk c of tile row r
-  constexpr int MASK = (BN / 8) % 8 == 0 ? 7 : 3;          // the XOR stays within the row's chunks
-  static_assert(BN / 8 % (MASK + 1) == 0, "chunks per row");
-  return r * (BN / 8) + (c ^ (r & MASK));
+  constexpr int MASK = (BN / E) % 8 == 0 ? 7 : 3;          // the XOR stays within the row's chunks
+  static_assert(BN / E % (MASK + 1) == 0, "chunks per row");
+  return r * (BN / E) + (c ^ (r & MASK));
 }
 
-template <int BM, int BN, int NT>
+// Eight consecutive elements as fp32 <-> 16-byte chunks.
+__device__ __forceinline__ void pack8(const float* f, uint4 (&v)[1]) {
+  uint32_t w[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) w[i] = (uint32_t)f2bf(f[2 * i]) | ((uint32_t)f2bf(f[2 * i + 1]) << 16);
+  v[0] = make_uint4(w[0], w[1], w[2], w[3]);
+}
+__device__ __forceinline__ void pack8(const float* f, uint4 (&v)[2]) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    v[i] = make_uint4(__float_as_uint(f[4 * i]), __float_as_uint(f[4 * i + 1]), __float_as_uint(f[4 * i + 2]),
+                      __float_as_uint(f[4 * i + 3]));
+}
+
+template <typename T, int BM, int BN, int NT>
 __device__ __forceinline__ void rope_kv_walk(const GemmP& p, int m0, int n0, int tid) {
   extern __shared__ uint4 lds[];
   constexpr int JG = BN / 16;                               // 16-column groups per tile row
@@ -293,7 +307,8 @@ __device__ __forceinline__ void rope_kv_walk(const GemmP& p, int m0, int n0, int
   const int part = n / QD, head = (n % QD) / hd;            // part 0 q, 1 k, 2 v
   const int d0 = (n % hd) / 2;                              // first pair of the group
   const bool rot = part < 2 && a.rope;
-  bf16* cache = reinterpret_cast<bf16*>(a.kv_layer);
+  constexpr int E = 16 / sizeof(T), NV = 8 / E;             // elements per chunk; chunks per half group
+  T* cache = reinterpret_cast<T*>(a.kv_layer);
   const size_t kv_off = (part == 2 ? a.st.kv : 0) + (size_t)head * a.st.head;
   const int rows = min(BM, p.M - m0);
   for (int rb = r0; rb < rows; rb += U * RS) {
@@ -314,28 +329,35 @@ __device__ __forceinline__ void rope_kv_walk(const GemmP& p, int m0, int n0, int
     for (int u = 0; u < U; ++u) {
       const int r = rb + u * RS;
       if (r >= rows) break;
-      uint4 lo = lds[tile_chunk<BN>(r, 2 * j)];
-      uint4 hi = lds[tile_chunk<BN>(r, 2 * j + 1)];
-      if (rot) {
-        float x0[8], x1[8];
-        Vec16<bf16>::unpack(lo, x0);
-        Vec16<bf16>::unpack(hi, x1);
-        uint32_t w0[4], w1[4];
+      uint4 lo[NV], hi[NV];
 #pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-          const float c0 = cs[u][e / 2].x, s0 = cs[u][e / 2].y, c1 = cs[u][e / 2].z, s1 = cs[u][e / 2].w;
-          const bf16 a0 = f2bf(x0[e] * c0 - x1[e] * s0), b0 = f2bf(x0[e] * s0 + x1[e] * c0);
-          const bf16 a1 = f2bf(x0[e + 1] * c1 - x1[e + 1] * s1), b1 = f2bf(x0[e + 1] * s1 + x1[e + 1] * c1);
-          w0[e / 2] = (uint32_t)a0 | ((uint32_t)a1 << 16);
-          w1[e / 2] = (uint32_t)b0 | ((uint32_t)b1 << 16);
-        }
-        lo = make_uint4(w0[0], w0[1], w0[2], w0[3]);
-        hi = make_uint4(w1[0], w1[1], w1[2], w1[3]);
+      for (int i = 0; i < NV; ++i) {
+        lo[i] = lds[tile_chunk<BN, E>(r, 2 * NV * j + i)];
+        hi[i] = lds[tile_chunk<BN, E>(r, 2 * NV * j + NV + i)];
       }
-      bf16* dst = part == 0 ? reinterpret_cast<bf16*>(p.out) + (size_t)(m0 + r) * p.N + (n - n % hd)
-                            : cache + (size_t)slot[u] * a.st.slot + kv_off + (size_t)pos[u] * a.st.pos;
-      *reinterpret_cast<uint4*>(dst + d0) = lo;
-      *reinterpret_cast<uint4*>(dst + half + d0) = hi;
+      if (rot) {
+        float x0[8], x1[8], y0[8], y1[8];
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+          Vec16<T>::unpack(lo[i], x0 + E * i);
+          Vec16<T>::unpack(hi[i], x1 + E * i);
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float c = e & 1 ? cs[u][e / 2].z : cs[u][e / 2].x, sn = e & 1 ? cs[u][e / 2].w : cs[u][e / 2].y;
+          y0[e] = x0[e] * c - x1[e] * sn;
+          y1[e] = x0[e] * sn + x1[e] * c;
+        }
+        pack8(y0, lo);
+        pack8(y1, hi);
+      }
+      T* dst = part == 0 ? reinterpret_cast<T*>(p.out) + (size_t)(m0 + r) * p.N + (n - n % hd)
+                         : cache + (size_t)slot[u] * a.st.slot + kv_off + (size_t)pos[u] * a.st.pos;
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        *reinterpret_cast<uint4*>(dst + d0 + E * i) = lo[i];
+        *reinterpret_cast<uint4*>(dst + half + d0 + E * i) = hi[i];
+      }
     }
   }
 }
@@ -355,7 +377,6 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
   constexpr int ES = sizeof(T);
   constexpr int BK = 128 / ES;
   constexpr bool F32 = ES == 4;
-  static_assert(!F32 || EPI != EPI_ROPE_KV, "the RoPE epilogue is bf16");
   constexpr int WTM = BM / WGM, WTN = BN / WGN;
   constexpr int FM = WTM / 16, FN = WTN / 16;
   constexpr int ROWS = BM + BN;
@@ -364,7 +385,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
   static_assert(BM % 8 == 0 && BN % 8 == 0 && ILO > 0, "8-row groups");
   static_assert(WTM % 16 == 0 && WTN % 16 == 0 && (EPI != EPI_SWIGLU || FN % 2 == 0), "wave tile");
   static_assert((S - 2) * IHI < 64 && S >= 2, "stages");
-  static_assert(BM * BN * 2 <= S * ROWS * 128, "the RoPE epilogue stages the bf16 tile in the ring's LDS");
+  static_assert(EPI != EPI_ROPE_KV || BM * BN * ES <= S * ROWS * 128, "the RoPE epilogue stages the tile in the ring's LDS");
   extern __shared__ uint4 lds[];                 // [S][ROWS * 8] 16-byte chunks
 
   const int per = gridDim.x / 8;
@@ -542,7 +563,8 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
   }
 
   if constexpr (EPI == EPI_ROPE_KV) {
-    bf16* t16 = reinterpret_cast<bf16*>(lds);
+    constexpr int E = 16 / ES;
+    T* tile = reinterpret_cast<T*>(lds);
 #pragma unroll
     for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
@@ -551,11 +573,11 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
 #pragma unroll
         for (int fn = 0; fn < FN; ++fn) {
           const int c = wn * WTN + fn * 16 + (lane & 15);
-          t16[tile_chunk<BN>(r, c >> 3) * 8 + (c & 7)] = f2bf(acc[fm][fn][i]);
+          tile[tile_chunk<BN, E>(r, c / E) * E + c % E] = from_f<T>(acc[fm][fn][i]);
         }
       }
     lds_read_barrier();                  // the producers pass their last barrier too
-    rope_kv_walk<BM, BN, 64 * NC>(p, m0, tile_n * BN, tid);
+    rope_kv_walk<T, BM, BN, 64 * NC>(p, m0, tile_n * BN, tid);
     return;
   }
 #pragma unroll
@@ -896,7 +918,7 @@ __global__ __launch_bounds__(512, 2) void gemm_quad_kernel(GemmP p) {
       }
     lds_read_barrier();
     if constexpr (EPI == EPI_ROPE_KV) {
-      rope_kv_walk<BM, BN, 512>(p, m0, tile_n * BN, te);
+      rope_kv_walk<bf16, BM, BN, 512>(p, m0, tile_n * BN, te);
     } else {
       constexpr int CH = BO / 8;                    // 16-byte chunks per row
       bf16* out = reinterpret_cast<bf16*>(p.out);
@@ -1183,6 +1205,7 @@ static hipError_t run_ws_f32(int epi, int cfg, const GemmP& p, hipStream_t s) {
     case EPI_SWIGLU: return run_ws_f32_cfg<EPI_SWIGLU>(cfg, p, s);
     case EPI_RESID_TO_F32: return run_ws_f32_cfg<EPI_RESID_TO_F32>(cfg, p, s);
     case EPI_RESIDF32_TO_ACT: return run_ws_f32_cfg<EPI_RESIDF32_TO_ACT>(cfg, p, s);
+    case EPI_ROPE_KV: return run_ws_f32_cfg<EPI_ROPE_KV>(cfg, p, s);
     default: return run_ws_f32_cfg<EPI_PARTIAL>(cfg, p, s);
   }
 }
@@ -1311,7 +1334,15 @@ hipError_t launch_linear(int dtype, const LinearArgs& a, hipStream_t s, int forc
     }
     const bool split = p.n_split > 1;
     if (split) p.out = a.parts;
+    // preproj with the rotary embedding and KV append in its epilogue
+    const bool rope = ws && a.kind == LIN_PLAIN && a.rope != nullptr && a.rope->hd % 16 == 0 &&
+                      a.N == 3 * a.rope->nh * a.rope->hd;
+    if (rope) {
+      p.rope = *a.rope;
+      if (a.rope_done) *a.rope_done = true;
+    }
     const int epi = split                      ? EPI_PARTIAL
+                    : rope                     ? EPI_ROPE_KV
                     : a.kind == LIN_PLAIN      ? EPI_STORE
                     : a.kind == LIN_GELU       ? EPI_GELU
                     : a.kind == LIN_SWIGLU     ? EPI_SWIGLU

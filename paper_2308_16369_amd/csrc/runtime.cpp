@@ -448,11 +448,11 @@ int layer_body(const Ctx& c, const sarathi_layer_weights* w, int layer, const vo
   float* hres = reinterpret_cast<float*>(ws + c.L.hres);
   float* parts = reinterpret_cast<float*>(ws + c.L.parts);
   const size_t parts_cap = (size_t)MAX_SPLIT * std::min(T, PARTS_ROWS) * H;
-  // the rotary table: hd/2 (cos, sin) pairs per row in the 2 QD bf16 columns
-  // behind a qkv row's q (written with the first layer's norm_1; no layer's
-  // fused preproj writes there)
-  float2* rope_tab = reinterpret_cast<float2*>(ws + c.L.qkv + (size_t)QD * 2);
-  const size_t rope_stride = (size_t)3 * QD * 2 / sizeof(float2);
+  // the rotary table: hd/2 (cos, sin) pairs per row in the 2 QD columns behind
+  // a qkv row's q (written with the first layer's norm_1; no layer's fused
+  // preproj writes there)
+  float2* rope_tab = reinterpret_cast<float2*>(ws + c.L.qkv + QD * esize(cfg));
+  const size_t rope_stride = 3 * QD * esize(cfg) / sizeof(float2);
   char* kv_layer = static_cast<char*>(c.kv->mem) + (size_t)layer * c.kv->st.layer * esize(cfg);
   hipError_t e;
   hipEvent_t* ev = prof_claim();
@@ -472,7 +472,7 @@ int layer_body(const Ctx& c, const sarathi_layer_weights* w, int layer, const vo
     MetaChunk first;
     meta_chunk(P, 0, &first);
     RopeTable rt{};
-    if (dt == SARATHI_BF16 && cfg->rope) rt = RopeTable{rope_tab, rope_stride, hd, cfg->rope_base, (int)P.o_pos};
+    if (cfg->rope) rt = RopeTable{rope_tab, rope_stride, hd, cfg->rope_base, (int)P.o_pos};
     e = launch_norm(dt, false, ln, x_in, w->norm1_g, w->norm1_b, ws + c.L.a, T, H, cfg->eps, c.s, &first,
                     reinterpret_cast<int*>(ws + c.L.meta), rt);
   } else {
@@ -481,7 +481,7 @@ int layer_body(const Ctx& c, const sarathi_layer_weights* w, int layer, const vo
   if (e != hipSuccess) return hip_fail(e, "norm_1");
 
   // preproj over all rows, with the rotary embedding and the in-place KV
-  // append in its epilogue (bf16)
+  // append in its epilogue
   SARATHI_MARK();
   RopeArgs ra{};
   ra.qkv = ws + c.L.qkv; ra.T = T; ra.nh = nh; ra.hd = hd; ra.rope = cfg->rope; ra.base = cfg->rope_base;
