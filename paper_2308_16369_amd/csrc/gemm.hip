@@ -34,6 +34,8 @@ struct GemmP {
                         // rotate their k-tile order
   void* out;            // [M, N]: dtype, or fp32 for EPI_RESID_TO_F32; EPI_PARTIAL: fp32 [n_split][M, N]
   const void* resid;    // EPI_RESID_TO_F32: dtype [M,N]; EPI_RESIDF32_TO_ACT: fp32 [M,N]
+  int wide_blocks;      // gemm_quad_kernel with a tail: blocks of the wide tiles (a multiple of 8), then
+  int tail_tiles, tail_n0;   // tail_tiles narrower tiles of the output columns from tail_n0
   int stream_w;         // gemm_ws_kernel: W is read once (one M-tile) and loaded non-temporally
   int vec4, vec8;       // N a multiple of 4 / 8 and out, resid 16-byte aligned: wide stores
   RopeArgs rope;        // EPI_ROPE_KV: rotary embedding + KV append of the preproj output
@@ -678,8 +680,9 @@ __device__ __forceinline__ void epi_store4(const GemmP& p, int r, int c, const f
   }
 }
 
+// One tile: output columns from n0_out.
 template <int FM, int FN, int EPI>
-__global__ __launch_bounds__(512, 2) void gemm_quad_kernel(GemmP p) {
+__device__ __forceinline__ void quad_tile(const GemmP& p, int tile_m, int split, int n0_out) {
   constexpr int WGM = 2, WGN = 4, BM = WGM * FM * 16, BN = WGN * FN * 16, BK = 64;
   constexpr int WTM = FM * 16, WTN = FN * 16;
   constexpr int FM0 = (FM + 1) / 2, FM1 = FM / 2, FN0 = (FN + 1) / 2, FN1 = FN / 2;   // 16-row groups per half
@@ -696,18 +699,9 @@ __global__ __launch_bounds__(512, 2) void gemm_quad_kernel(GemmP p) {
   // at the same place in both halves (a smaller second half leaves gaps), so
   // one LDS address per operand and k-step serves both
   extern __shared__ uint4 lds[];
-  const int per = gridDim.x / 8;
-  const int t = (blockIdx.x % 8) * per + blockIdx.x / 8;
-  if (t >= p.n_tiles) return;
-  const int tile_m = t % p.tiles_m;
-  const int rest = t / p.tiles_m;
-  const int split = rest % p.n_split;
-  const int tile_n = rest / p.n_split;
-
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
   const int m0 = tile_m * BM;
-  const int n0_out = tile_n * (EPI == EPI_SWIGLU ? BN / 2 : BN);
   const int kbeg = split * p.k_split;
   const int kend = min(p.K, kbeg + p.k_split);
   const int nk = (kend - kbeg) / BK;
@@ -918,7 +912,7 @@ __global__ __launch_bounds__(512, 2) void gemm_quad_kernel(GemmP p) {
       }
     lds_read_barrier();
     if constexpr (EPI == EPI_ROPE_KV) {
-      rope_kv_walk<bf16, BM, BN, 512>(p, m0, tile_n * BN, te);
+      rope_kv_walk<bf16, BM, BN, 512>(p, m0, n0_out, te);
     } else {
       constexpr int CH = BO / 8;                    // 16-byte chunks per row
       bf16* out = reinterpret_cast<bf16*>(p.out);
@@ -949,6 +943,33 @@ __global__ __launch_bounds__(512, 2) void gemm_quad_kernel(GemmP p) {
       if (r < p.M && c < p.N) epi_store4<EPI>(p, r, c, acc[fm][fn], split);
     }
   }
+}
+
+// Tiles of FN groups per wave, XCD-aware order as in gemm_ws_kernel; behind them
+// (FT > 0) the tail: the columns from p.tail_n0 on as tiles of FT groups.  Whole
+// rounds of one block per CU take the wide tiles and the rest one round of
+// narrower ones, where a last round of wide tiles would leave CUs idle
+// (LLaMA-13B ffn_ln1 at 1021 rows: 432 wide tiles are 1.69 rounds; 256 and a
+// tail of 236: layer 640 -> 627 us; LLaMA-33B at 544 rows 924 -> 906).
+template <int FM, int FN, int FT, int EPI>
+__global__ __launch_bounds__(512, 2) void gemm_quad_kernel(GemmP p) {
+  int b = blockIdx.x, blocks = gridDim.x;
+  if constexpr (FT > 0) {
+    if (b >= p.wide_blocks) {
+      b -= p.wide_blocks;
+      blocks -= p.wide_blocks;
+      const int t = (b % 8) * (blocks / 8) + b / 8;
+      if (t >= p.tail_tiles) return;
+      quad_tile<FM, FT, EPI>(p, t % p.tiles_m, 0, p.tail_n0 + t / p.tiles_m * (EPI == EPI_SWIGLU ? 32 * FT : 64 * FT));
+      return;
+    }
+    blocks = p.wide_blocks;
+  }
+  const int t = (b % 8) * (blocks / 8) + b / 8;
+  if (t >= p.n_tiles) return;
+  const int rest = t / p.tiles_m;
+  quad_tile<FM, FN, EPI>(p, t % p.tiles_m, rest % p.n_split,
+                         rest / p.n_split * (EPI == EPI_SWIGLU ? 32 * FN : 64 * FN));
 }
 
 // ============================================================================ fp32 FMA
@@ -1071,17 +1092,27 @@ static hipError_t run_ws(const GemmP& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int FM, int FN, int EPI>
-static hipError_t run_quad(const GemmP& p, hipStream_t s) {
+constexpr int QUAD_TAIL = 3;   // a tail's tiles: 192 W rows
+template <int FM, int FN, int FT, int EPI>
+static hipError_t run_quad_as(const GemmP& p, hipStream_t s) {
   // two stages of two halves (the RoPE epilogue's tile fits there)
   constexpr int ROWS0 = (2 * ((FM + 1) / 2) + 4 * ((FN + 1) / 2)) * 16;   // rows of a half stage
+  static_assert((FT + 1) / 2 <= (FN + 1) / 2, "the tail's tiles need no more LDS");
   const size_t lds_bytes = (size_t)4 * ROWS0 * 128;
   static std::atomic<uint64_t> lds_set{0};   // devices on which this instance's LDS limit is raised
-  hipError_t e = ensure_dynamic_lds((const void*)gemm_quad_kernel<FM, FN, EPI>, (int)lds_bytes, lds_set);
+  hipError_t e = ensure_dynamic_lds((const void*)gemm_quad_kernel<FM, FN, FT, EPI>, (int)lds_bytes, lds_set);
   if (e != hipSuccess) return e;
-  const int grid = (p.n_tiles + 7) / 8 * 8;
-  hipLaunchKernelGGL((gemm_quad_kernel<FM, FN, EPI>), dim3(grid), dim3(512), lds_bytes, s, p);
+  const int grid = FT > 0 ? p.wide_blocks + (p.tail_tiles + 7) / 8 * 8 : (p.n_tiles + 7) / 8 * 8;
+  hipLaunchKernelGGL((gemm_quad_kernel<FM, FN, FT, EPI>), dim3(grid), dim3(512), lds_bytes, s, p);
   return hipGetLastError();
+}
+
+template <int FM, int FN, int EPI>
+static hipError_t run_quad(const GemmP& p, bool tail, hipStream_t s) {
+  if constexpr (FN == 4 && EPI != EPI_PARTIAL) {
+    if (tail) return run_quad_as<FM, FN, QUAD_TAIL, EPI>(p, s);
+  }
+  return run_quad_as<FM, FN, 0, EPI>(p, s);
 }
 
 template <int BM, int BN, int WGM, int WGN, int PD>
@@ -1145,7 +1176,7 @@ constexpr double kQuadTileUs[] = {1.27, 1.17, 1.5};   // their time per 64-wide 
 constexpr int kNumWsTiles = sizeof(kWsTiles) / sizeof(kWsTiles[0]);
 
 template <int EPI>
-static hipError_t run_ws_cfg(int cfg, const GemmP& p, hipStream_t s) {
+static hipError_t run_ws_cfg(int cfg, const GemmP& p, bool tail, hipStream_t s) {
   switch (cfg) {
     case 0: return run_ws<bf16, 64, 64, 2, 2, 4, 6, EPI>(p, s);
     case 1: return run_ws<bf16, 64, 128, 2, 4, 4, 6, EPI>(p, s);
@@ -1161,21 +1192,21 @@ static hipError_t run_ws_cfg(int cfg, const GemmP& p, hipStream_t s) {
     case 11: return run_ws<bf16, 160, 192, 2, 6, 4, 3, EPI>(p, s);
     case 12: return run_ws<bf16, 160, 224, 2, 7, 2, 3, EPI>(p, s);
     case 13: return run_ws<bf16, 160, 256, 2, 4, 4, 3, EPI>(p, s);
-    case 14: return run_quad<9, 3, EPI>(p, s);
-    case 15: return run_quad<6, 4, EPI>(p, s);
-    default: return run_quad<8, 4, EPI>(p, s);
+    case 14: return run_quad<9, 3, EPI>(p, tail, s);
+    case 15: return run_quad<6, 4, EPI>(p, tail, s);
+    default: return run_quad<8, 4, EPI>(p, tail, s);
   }
 }
 
-static hipError_t run_ws_epi(int epi, int cfg, const GemmP& p, hipStream_t s) {
+static hipError_t run_ws_epi(int epi, int cfg, const GemmP& p, bool tail, hipStream_t s) {
   switch (epi) {
-    case EPI_STORE: return run_ws_cfg<EPI_STORE>(cfg, p, s);
-    case EPI_GELU: return run_ws_cfg<EPI_GELU>(cfg, p, s);
-    case EPI_SWIGLU: return run_ws_cfg<EPI_SWIGLU>(cfg, p, s);
-    case EPI_RESID_TO_F32: return run_ws_cfg<EPI_RESID_TO_F32>(cfg, p, s);
-    case EPI_RESIDF32_TO_ACT: return run_ws_cfg<EPI_RESIDF32_TO_ACT>(cfg, p, s);
-    case EPI_ROPE_KV: return run_ws_cfg<EPI_ROPE_KV>(cfg, p, s);
-    default: return run_ws_cfg<EPI_PARTIAL>(cfg, p, s);
+    case EPI_STORE: return run_ws_cfg<EPI_STORE>(cfg, p, tail, s);
+    case EPI_GELU: return run_ws_cfg<EPI_GELU>(cfg, p, tail, s);
+    case EPI_SWIGLU: return run_ws_cfg<EPI_SWIGLU>(cfg, p, tail, s);
+    case EPI_RESID_TO_F32: return run_ws_cfg<EPI_RESID_TO_F32>(cfg, p, tail, s);
+    case EPI_RESIDF32_TO_ACT: return run_ws_cfg<EPI_RESIDF32_TO_ACT>(cfg, p, tail, s);
+    case EPI_ROPE_KV: return run_ws_cfg<EPI_ROPE_KV>(cfg, p, tail, s);
+    default: return run_ws_cfg<EPI_PARTIAL>(cfg, p, tail, s);
   }
 }
 
@@ -1222,6 +1253,7 @@ static hipError_t run_ws_f32(int epi, int cfg, const GemmP& p, hipStream_t s) {
 // at ~5.5 TB/s.
 struct WsChoice {
   int cfg, n_split;
+  int wide_n = 0;      // quadrant tiles: > 0, that many W panels of them and a tail of narrower tiles
 };
 static WsChoice pick_ws(int M, int N, int K, bool swiglu, int max_split) {
   WsChoice best{10, 1};
@@ -1251,6 +1283,18 @@ static WsChoice pick_ws(int M, int N, int K, bool swiglu, int max_split) {
         best_t = t;
         best = {c, ns};
       }
+    }
+    // 256-wide quadrant tiles whose last round is not full: whole rounds of
+    // them, then one round of 192-wide tiles over the columns left
+    if (c < kFirstQuadTile || bn != 256 || tiles <= 256 || tiles % 256 == 0) continue;
+    const int rounds = (int)(tiles / 256), wide_n = rounds * 256 / tiles_m;
+    const int pert = per / 4 * QUAD_TAIL, left = N - wide_n * per;
+    if (left <= 0 || (long)tiles_m * ((left + pert - 1) / pert) > 256) continue;
+    const double out_us = (double)bm * per * 2.0 / 4.0e4;
+    const double t = rounds * (nk * per_k + 3.0 + out_us) + nk * (bm == 256 ? 1.15 : 0.95) + 3.0 + out_us * 0.75;
+    if (t < best_t * 0.999) {
+      best_t = t;
+      best = {c, 1, wide_n};
     }
   }
   return best;
@@ -1392,12 +1436,13 @@ hipError_t launch_linear(int dtype, const LinearArgs& a, hipStream_t s, int forc
     max_split = (int)std::min<size_t>((size_t)max_split, a.parts_cap / ((size_t)a.M * a.N));
     max_split = std::max(max_split, 1);
   }
-  int cfg, BM, BN, ws_split = 1;
+  int cfg, BM, BN, ws_split = 1, wide_n = 0;
   if (ws) {
     WsChoice ch = pick_ws(a.M, a.N, a.K, swiglu, max_split);
     if (force_tile >= 0 && force_tile < kNumWsTiles) ch = {force_tile, std::min(std::max(force_split, 1), max_split)};
     cfg = ch.cfg;
     ws_split = ch.n_split;
+    wide_n = ch.wide_n;
     BM = kWsTiles[cfg].bm;
     BN = kWsTiles[cfg].bn;
   } else {
@@ -1443,6 +1488,13 @@ hipError_t launch_linear(int dtype, const LinearArgs& a, hipStream_t s, int forc
       p.out = a.parts;
     }
   }
+  if (wide_n > 0) {
+    const int per_tail = out_per_tile / 4 * QUAD_TAIL;
+    p.tail_n0 = wide_n * out_per_tile;
+    p.tail_tiles = p.tiles_m * ((a.N - p.tail_n0 + per_tail - 1) / per_tail);
+    p.tiles_n = wide_n;
+    p.wide_blocks = (p.tiles_m * wide_n + 7) / 8 * 8;
+  }
   p.n_tiles = p.tiles_m * p.tiles_n * p.n_split;
   p.vec4 = a.N % 4 == 0 && ((reinterpret_cast<uintptr_t>(p.out) | reinterpret_cast<uintptr_t>(p.resid)) & 15) == 0;
   p.vec8 = p.vec4 && a.N % 8 == 0;
@@ -1467,7 +1519,7 @@ hipError_t launch_linear(int dtype, const LinearArgs& a, hipStream_t s, int forc
   }
   hipError_t e;
   if (ws) {
-    e = run_ws_epi(epi, cfg, p, s);
+    e = run_ws_epi(epi, cfg, p, wide_n > 0, s);
   } else {
     switch (cfg) {
       case CFG_320x128: e = run_bf16_epi<320, 128, 4, 2, 2>(epi, p, s); break;
