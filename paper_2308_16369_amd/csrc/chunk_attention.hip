@@ -12,7 +12,8 @@
 // PREFILL_QBLOCK_SMALL (4 waves), chosen per batch by the plan.  K and V tiles of 64
 // keys are staged in LDS rings by LDS DMA (V read back transposed so P*V
 // takes 16 contiguous bytes per lane); S = Q K^T and O += P V run on
-// v_mfma_f32_32x32x16_bf16 with an fp32 online softmax.
+// v_mfma_f32_32x32x16_bf16 with an fp32 online softmax.  fp32: blocks of 64
+// queries on v_mfma_f32_16x16x4_f32 (attn_prefill_f32_kernel).
 #include "kernels.h"
 
 namespace sarathi {

@@ -9,11 +9,19 @@
 // K-contiguous, so every lane moves 16 contiguous bytes.  Epilogues fuse the
 // residual add (postproj, ffn_ln2), SiLU*mul (SwiGLU ffn_ln1) and GELU.
 // Split-K stores one fp32 partial per split; a separate pass adds residual +
-// partials in a fixed order, so results do not depend on scheduling.
+// partials in a fixed order, so results do not depend on scheduling.  Large
+// batches: gemm_quad_kernel, tiles of up to 256 x 256.  fp32: gemm_ws_kernel on
+// v_mfma_f32_16x16x4_f32.
 //
-// bf16 with a ragged K: gemm_bf16_kernel, the same tiles loaded through
-// registers (k-chunks past K zeroed).  fp32: a plain LDS-tiled FMA kernel
-// with the same epilogues.
+// What bounds these: a CU keeps ~45 KB of loads in flight whatever the ring
+// depth or the number of producers, and returns them in order, so operand rows
+// that hit in L2 wait behind weight rows that come from HBM: ~30 bytes per
+// clock and CU (64 when everything hits).  Under full matrix load the power
+// limit holds the clock at 1.7-2.1 GHz, which slows that path too.
+//
+// bf16 with a ragged K, or operands of 4 GiB and more: gemm_bf16_kernel, tiles
+// loaded through registers (k-chunks past K zeroed).  fp32 operands of 4 GiB
+// and more: a plain LDS-tiled FMA kernel.
 #include "kernels.h"
 
 #include <algorithm>

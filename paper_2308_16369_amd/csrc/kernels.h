@@ -97,8 +97,7 @@ constexpr int MAX_SPLIT = 6;   // split-K partials: at most MAX_SPLIT x [M, N] f
 // shape with force_split K-splits (residual kinds with scratch) instead of the
 // cost model's choice.
 // With plan non-null nothing is launched: *plan receives the block shape and
-// K-split count the op would run with (bm = bn = 0 for the fp32 kernel's
-// 64 x 64 tiles is reported as 64, 64).
+// K-split count the op would run with.
 struct LinearPlan {
   int bm, bn, n_split;
 };
