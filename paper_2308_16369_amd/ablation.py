@@ -416,7 +416,7 @@ def tile_sweep(shape, T: int, iters: int = 20) -> List[dict]:
             continue
         for tile in range(S.sarathi_linear_tile_count()):
             bm, bn = S.sarathi_linear_tile_shape(tile)
-            if bm == 64 and T > 64:
+            if bm == 64 and T > 128:    # the planner takes 64-row tiles up to 128 rows
                 continue
             for ns in splits:
                 run = lambda: S.sarathi_linear_tiled(kind, T, N, K, x.data_ptr(), w.data_ptr(), resid.data_ptr(),
