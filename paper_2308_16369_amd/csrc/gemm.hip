@@ -455,7 +455,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
 #pragma unroll
       for (int j = IHI - 1; j >= 0; --j)
         if (j < ILO || extra)
-          load(min(j * NP + q, ROWS / 8 - 1) < GA, a_k + off[j] - back, w_k + off[j] - back, dst + (j * NP + q) * 64);
+          load(min(j * NP + q, ROWS / 8 - 1) < GA, a_k, w_k, off[j] - back, dst + (j * NP + q) * 64);
     };
     auto wait_next = [&](bool all) {   // all but the newest S - 2 stages landed
       if (all) wait_vmcnt<0>();
@@ -478,12 +478,12 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
       }
     };
     if (p.stream_w)
-      produce([](bool is_a, const char* a, const char* w, uint4* d) {
-        if (is_a) dma16(a, d);
-        else dma16_stream(w, d);
+      produce([](bool is_a, const char* a, const char* w, uint32_t at, uint4* d) {
+        if (is_a) dma16(a + at, d);
+        else dma16_stream(w + at, d);
       });
     else
-      produce([](bool is_a, const char* a, const char* w, uint4* d) { dma16(is_a ? a : w, d); });
+      produce([](bool is_a, const char* a, const char* w, uint32_t at, uint4* d) { dma16((is_a ? a : w) + at, d); });
     if constexpr (EPI == EPI_ROPE_KV) lds_barrier();   // pairs with the consumers' epilogue barrier
     return;
   }
