@@ -44,7 +44,6 @@ struct GemmP {
   const void* resid;    // EPI_RESID_TO_F32: dtype [M,N]; EPI_RESIDF32_TO_ACT: fp32 [M,N]
   int wide_blocks;      // gemm_quad_kernel with a tail: blocks of the wide tiles (a multiple of 8), then
   int tail_tiles, tail_n0;   // tail_tiles narrower tiles of the output columns from tail_n0
-  int stream_w;         // gemm_ws_kernel: W is read once (one M-tile) and loaded non-temporally
   int vec4, vec8;       // N a multiple of 4 / 8 and out, resid 16-byte aligned: wide stores
   RopeArgs rope;        // EPI_ROPE_KV: rotary embedding + KV append of the preproj output
 };
@@ -381,7 +380,12 @@ __device__ __forceinline__ void rope_kv_walk(const GemmP& p, int m0, int n0, int
 // the last k-tile's chunks past K are read from the row's last chunk and
 // zeroed in registers.  Bound by the fp32 matrix rate (157 TFLOP/s), 8x the
 // time per operand byte of bf16.
-template <typename T, int BM, int BN, int WGM, int WGN, int NP, int S, int EPI>
+//
+// STREAM: W is loaded non-temporally (read once: one M-tile).  A template
+// argument and not a run-time choice: with both producer loops in one kernel
+// the 224-wide tiles (22 or 24 requests per wave and k-tile) spill 17-49
+// scalar registers, in launches that never stream too.
+template <typename T, int BM, int BN, int WGM, int WGN, int NP, int S, int EPI, bool STREAM>
 __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p) {
   constexpr int NC = WGM * WGN;
   constexpr int ES = sizeof(T);
@@ -441,7 +445,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
     // HBM latency -- and found in L2 by the others a step later, instead of
     // all G waiting on the same miss.
     const int G = p.rotate_k ? p.tiles_m : 1, RD = p.rotate_k, GR = G * RD;
-    auto issue = [&](int stage, int kt, auto load) {
+    auto issue = [&](int stage, int kt) {
       if (G > 1) {
         const int base = kt / GR * GR;
         if (base + GR <= nk) kt = base + (kt - base + tile_m * RD) % GR;
@@ -454,36 +458,31 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
           F32 && kbeg + (kt + 1) * BK > kend ? 16u * max(lchunk - ((kend - kbeg - kt * BK) / 4 - 1), 0) : 0u;
 #pragma unroll
       for (int j = IHI - 1; j >= 0; --j)
-        if (j < ILO || extra)
-          load(min(j * NP + q, ROWS / 8 - 1) < GA, a_k, w_k, off[j] - back, dst + (j * NP + q) * 64);
+        if (j < ILO || extra) {
+          // the matrix is chosen on the scalar bases, before the lane's offset
+          const bool is_a = min(j * NP + q, ROWS / 8 - 1) < GA;
+          if (STREAM && !is_a) dma16_stream(w_k + (off[j] - back), dst + (j * NP + q) * 64);
+          else dma16((is_a ? a_k : w_k) + (off[j] - back), dst + (j * NP + q) * 64);
+        }
     };
     auto wait_next = [&](bool all) {   // all but the newest S - 2 stages landed
       if (all) wait_vmcnt<0>();
       else if (extra) wait_vmcnt<(S - 2) * IHI>();
       else wait_vmcnt<(S - 2) * ILO>();
     };
-    auto produce = [&](auto load) {
 #pragma unroll
-      for (int st = 0; st < S - 1; ++st)
-        if (st < nk) issue(st, st, load);
-      wait_next(S - 2 >= nk);
+    for (int st = 0; st < S - 1; ++st)
+      if (st < nk) issue(st, st);
+    wait_next(S - 2 >= nk);
+    lds_barrier();
+    int nbuf = S - 1;
+    for (int kt = 0; kt < nk; ++kt) {
+      const bool more = kt + S - 1 < nk;
+      if (more) issue(nbuf, kt + S - 1);
+      wait_next(!more);
       lds_barrier();
-      int nbuf = S - 1;
-      for (int kt = 0; kt < nk; ++kt) {
-        const bool more = kt + S - 1 < nk;
-        if (more) issue(nbuf, kt + S - 1, load);
-        wait_next(!more);
-        lds_barrier();
-        nbuf = (nbuf + 1 == S) ? 0 : nbuf + 1;
-      }
-    };
-    if (p.stream_w)
-      produce([](bool is_a, const char* a, const char* w, uint32_t at, uint4* d) {
-        if (is_a) dma16(a + at, d);
-        else dma16_stream(w + at, d);
-      });
-    else
-      produce([](bool is_a, const char* a, const char* w, uint32_t at, uint4* d) { dma16((is_a ? a : w) + at, d); });
+      nbuf = (nbuf + 1 == S) ? 0 : nbuf + 1;
+    }
     if constexpr (EPI == EPI_ROPE_KV) lds_barrier();   // pairs with the consumers' epilogue barrier
     return;
   }
@@ -1088,16 +1087,24 @@ static hipError_t run_bf16(GemmP p, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename T, int BM, int BN, int WGM, int WGN, int NP, int S, int EPI>
-static hipError_t run_ws(const GemmP& p, hipStream_t s) {
+template <typename T, int BM, int BN, int WGM, int WGN, int NP, int S, int EPI, bool STREAM>
+static hipError_t run_ws_as(const GemmP& p, hipStream_t s) {
   const size_t lds_bytes = (size_t)S * (BM + BN) * 8 * sizeof(uint4);
   static std::atomic<uint64_t> lds_set{0};   // devices on which this instance's LDS limit is raised
-  hipError_t e = ensure_dynamic_lds((const void*)gemm_ws_kernel<T, BM, BN, WGM, WGN, NP, S, EPI>, (int)lds_bytes, lds_set);
+  hipError_t e = ensure_dynamic_lds((const void*)gemm_ws_kernel<T, BM, BN, WGM, WGN, NP, S, EPI, STREAM>, (int)lds_bytes, lds_set);
   if (e != hipSuccess) return e;
   const int grid = (p.n_tiles + 7) / 8 * 8;
-  hipLaunchKernelGGL((gemm_ws_kernel<T, BM, BN, WGM, WGN, NP, S, EPI>), dim3(grid), dim3(64 * (WGM * WGN + NP)),
-                     lds_bytes, s, p);
+  hipLaunchKernelGGL((gemm_ws_kernel<T, BM, BN, WGM, WGN, NP, S, EPI, STREAM>), dim3(grid),
+                     dim3(64 * (WGM * WGN + NP)), lds_bytes, s, p);
   return hipGetLastError();
+}
+
+template <typename T, int BM, int BN, int WGM, int WGN, int NP, int S, int EPI>
+static hipError_t run_ws(const GemmP& p, bool stream_w, hipStream_t s) {
+  if constexpr (sizeof(T) == 2) {
+    if (stream_w) return run_ws_as<T, BM, BN, WGM, WGN, NP, S, EPI, true>(p, s);
+  }
+  return run_ws_as<T, BM, BN, WGM, WGN, NP, S, EPI, false>(p, s);
 }
 
 constexpr int QUAD_TAIL = 3;   // a tail's tiles: 192 W rows
@@ -1183,38 +1190,44 @@ constexpr int kFirstQuadTile = 14;   // the rest run gemm_quad_kernel
 constexpr double kQuadTileUs[] = {1.27, 1.17, 1.5};   // their time per 64-wide k-tile
 constexpr int kNumWsTiles = sizeof(kWsTiles) / sizeof(kWsTiles[0]);
 
+// Variants of a launch: gemm_ws_kernel with W loaded non-temporally, and
+// gemm_quad_kernel with a tail of narrower tiles.
+struct WsLaunch {
+  bool stream_w, tail;
+};
+
 template <int EPI>
-static hipError_t run_ws_cfg(int cfg, const GemmP& p, bool tail, hipStream_t s) {
+static hipError_t run_ws_cfg(int cfg, const GemmP& p, const WsLaunch& how, hipStream_t s) {
   switch (cfg) {
-    case 0: return run_ws<bf16, 64, 64, 2, 2, 4, 6, EPI>(p, s);
-    case 1: return run_ws<bf16, 64, 128, 2, 4, 4, 6, EPI>(p, s);
-    case 2: return run_ws<bf16, 64, 256, 2, 4, 4, 3, EPI>(p, s);
-    case 3: return run_ws<bf16, 96, 128, 2, 4, 4, 5, EPI>(p, s);
-    case 4: return run_ws<bf16, 96, 192, 2, 6, 4, 4, EPI>(p, s);
-    case 5: return run_ws<bf16, 96, 256, 2, 4, 4, 3, EPI>(p, s);
-    case 6: return run_ws<bf16, 128, 128, 2, 4, 4, 4, EPI>(p, s);
-    case 7: return run_ws<bf16, 128, 192, 2, 6, 4, 3, EPI>(p, s);
-    case 8: return run_ws<bf16, 128, 224, 2, 7, 2, 3, EPI>(p, s);
-    case 9: return run_ws<bf16, 128, 256, 2, 4, 4, 3, EPI>(p, s);
-    case 10: return run_ws<bf16, 160, 128, 2, 4, 4, 4, EPI>(p, s);
-    case 11: return run_ws<bf16, 160, 192, 2, 6, 4, 3, EPI>(p, s);
-    case 12: return run_ws<bf16, 160, 224, 2, 7, 2, 3, EPI>(p, s);
-    case 13: return run_ws<bf16, 160, 256, 2, 4, 4, 3, EPI>(p, s);
-    case 14: return run_quad<9, 3, EPI>(p, tail, s);
-    case 15: return run_quad<6, 4, EPI>(p, tail, s);
-    default: return run_quad<8, 4, EPI>(p, tail, s);
+    case 0: return run_ws<bf16, 64, 64, 2, 2, 4, 6, EPI>(p, how.stream_w, s);
+    case 1: return run_ws<bf16, 64, 128, 2, 4, 4, 6, EPI>(p, how.stream_w, s);
+    case 2: return run_ws<bf16, 64, 256, 2, 4, 4, 3, EPI>(p, how.stream_w, s);
+    case 3: return run_ws<bf16, 96, 128, 2, 4, 4, 5, EPI>(p, how.stream_w, s);
+    case 4: return run_ws<bf16, 96, 192, 2, 6, 4, 4, EPI>(p, how.stream_w, s);
+    case 5: return run_ws<bf16, 96, 256, 2, 4, 4, 3, EPI>(p, how.stream_w, s);
+    case 6: return run_ws<bf16, 128, 128, 2, 4, 4, 4, EPI>(p, how.stream_w, s);
+    case 7: return run_ws<bf16, 128, 192, 2, 6, 4, 3, EPI>(p, how.stream_w, s);
+    case 8: return run_ws<bf16, 128, 224, 2, 7, 2, 3, EPI>(p, how.stream_w, s);
+    case 9: return run_ws<bf16, 128, 256, 2, 4, 4, 3, EPI>(p, how.stream_w, s);
+    case 10: return run_ws<bf16, 160, 128, 2, 4, 4, 4, EPI>(p, how.stream_w, s);
+    case 11: return run_ws<bf16, 160, 192, 2, 6, 4, 3, EPI>(p, how.stream_w, s);
+    case 12: return run_ws<bf16, 160, 224, 2, 7, 2, 3, EPI>(p, how.stream_w, s);
+    case 13: return run_ws<bf16, 160, 256, 2, 4, 4, 3, EPI>(p, how.stream_w, s);
+    case 14: return run_quad<9, 3, EPI>(p, how.tail, s);
+    case 15: return run_quad<6, 4, EPI>(p, how.tail, s);
+    default: return run_quad<8, 4, EPI>(p, how.tail, s);
   }
 }
 
-static hipError_t run_ws_epi(int epi, int cfg, const GemmP& p, bool tail, hipStream_t s) {
+static hipError_t run_ws_epi(int epi, int cfg, const GemmP& p, const WsLaunch& how, hipStream_t s) {
   switch (epi) {
-    case EPI_STORE: return run_ws_cfg<EPI_STORE>(cfg, p, tail, s);
-    case EPI_GELU: return run_ws_cfg<EPI_GELU>(cfg, p, tail, s);
-    case EPI_SWIGLU: return run_ws_cfg<EPI_SWIGLU>(cfg, p, tail, s);
-    case EPI_RESID_TO_F32: return run_ws_cfg<EPI_RESID_TO_F32>(cfg, p, tail, s);
-    case EPI_RESIDF32_TO_ACT: return run_ws_cfg<EPI_RESIDF32_TO_ACT>(cfg, p, tail, s);
-    case EPI_ROPE_KV: return run_ws_cfg<EPI_ROPE_KV>(cfg, p, tail, s);
-    default: return run_ws_cfg<EPI_PARTIAL>(cfg, p, tail, s);
+    case EPI_STORE: return run_ws_cfg<EPI_STORE>(cfg, p, how, s);
+    case EPI_GELU: return run_ws_cfg<EPI_GELU>(cfg, p, how, s);
+    case EPI_SWIGLU: return run_ws_cfg<EPI_SWIGLU>(cfg, p, how, s);
+    case EPI_RESID_TO_F32: return run_ws_cfg<EPI_RESID_TO_F32>(cfg, p, how, s);
+    case EPI_RESIDF32_TO_ACT: return run_ws_cfg<EPI_RESIDF32_TO_ACT>(cfg, p, how, s);
+    case EPI_ROPE_KV: return run_ws_cfg<EPI_ROPE_KV>(cfg, p, how, s);
+    default: return run_ws_cfg<EPI_PARTIAL>(cfg, p, how, s);
   }
 }
 
@@ -1227,13 +1240,13 @@ constexpr int kNumF32Tiles = sizeof(kF32Tiles) / sizeof(kF32Tiles[0]);
 template <int EPI>
 static hipError_t run_ws_f32_cfg(int cfg, const GemmP& p, hipStream_t s) {
   switch (cfg) {
-    case 0: return run_ws<float, 32, 32, 2, 1, 2, 6, EPI>(p, s);
-    case 1: return run_ws<float, 32, 64, 2, 2, 2, 6, EPI>(p, s);
-    case 2: return run_ws<float, 64, 64, 2, 2, 4, 6, EPI>(p, s);
-    case 3: return run_ws<float, 96, 64, 2, 2, 4, 5, EPI>(p, s);
-    case 4: return run_ws<float, 160, 64, 2, 2, 4, 4, EPI>(p, s);
-    case 5: return run_ws<float, 96, 128, 2, 4, 4, 4, EPI>(p, s);
-    default: return run_ws<float, 160, 128, 2, 4, 4, 3, EPI>(p, s);
+    case 0: return run_ws<float, 32, 32, 2, 1, 2, 6, EPI>(p, false, s);
+    case 1: return run_ws<float, 32, 64, 2, 2, 2, 6, EPI>(p, false, s);
+    case 2: return run_ws<float, 64, 64, 2, 2, 4, 6, EPI>(p, false, s);
+    case 3: return run_ws<float, 96, 64, 2, 2, 4, 5, EPI>(p, false, s);
+    case 4: return run_ws<float, 160, 64, 2, 2, 4, 4, EPI>(p, false, s);
+    case 5: return run_ws<float, 96, 128, 2, 4, 4, 4, EPI>(p, false, s);
+    default: return run_ws<float, 160, 128, 2, 4, 4, 3, EPI>(p, false, s);
   }
 }
 
@@ -1511,7 +1524,7 @@ hipError_t launch_linear(int dtype, const LinearArgs& a, hipStream_t s, int forc
   // 6.4 TB/s; LLaMA-33B 160 rows ffn_ln1 107 -> 97; GPT-3 30 rows ffn_ln2 215 ->
   // 189; the quadrant tiles gain nothing).  Not below 32 MB: the weights of such a model can stay in the 256 MB
   // memory-side cache from call to call.  Two M-tiles meet in L2 instead.
-  p.stream_w = ws && cfg < kFirstQuadTile && p.tiles_m == 1 && w_rows * a.K * 2 >= (32u << 20);
+  const bool stream_w = ws && cfg < kFirstQuadTile && p.tiles_m == 1 && w_rows * a.K * 2 >= (32u << 20);
   // Rotated k order for the two M-tiles of a W panel, when a block runs at
   // most 192 k-tiles.  Measured in the layers: LLaMA-13B preproj -13% and
   // ffn_ln1 -2%; LLaMA-33B at 288 rows every op -2..-5% (layer -4%); GPT-3
@@ -1527,7 +1540,7 @@ hipError_t launch_linear(int dtype, const LinearArgs& a, hipStream_t s, int forc
   }
   hipError_t e;
   if (ws) {
-    e = run_ws_epi(epi, cfg, p, wide_n > 0, s);
+    e = run_ws_epi(epi, cfg, p, WsLaunch{stream_w, wide_n > 0}, s);
   } else {
     switch (cfg) {
       case CFG_320x128: e = run_bf16_epi<320, 128, 4, 2, 2>(epi, p, s); break;
