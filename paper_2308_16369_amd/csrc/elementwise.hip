@@ -135,22 +135,30 @@ __global__ __launch_bounds__(256) void norm_kernel(const Tin* __restrict__ in, c
 
 // The first norm of a layer call with the metadata upload riding along:
 // block 0 copies the metadata chunk (as meta_write_kernel), blocks 1..rows
-// normalise rows 0..rows-1.  One launch instead of two.  A fifth wave, when
-// launched, fills the row's part of the rotary table: once per row and call
-// instead of once per row, head and layer in the preproj epilogue.
+// normalise rows 0..rows-1.  One launch instead of two.  With rope.tab the
+// row's part of the rotary table is filled too, once per row and call instead
+// of once per row, head and layer in the preproj epilogue: by a fifth wave, or
+// by the first one after its row in the widest instance, whose registers need
+// the four-wave bound (with five, two waves share a SIMD's register file and
+// the LayerNorm kernel spilled 11 registers).
+constexpr int norm_rope_threads(int nc) { return nc == NORM_NC ? 256 : 320; }
+
+__device__ __forceinline__ void rope_table_row(const RopeTable& rope, const MetaChunk& c, const int* dst, int row,
+                                               int i) {
+  if (i >= rope.hd / 2) return;
+  const int at = rope.pos_at + row;                 // metadata past this chunk is already at dst
+  const int pos = at < META_CHUNK ? c.values[at] : dst[at];
+  float sn, cs;
+  rope_sincos(pos, rope_theta(i, rope.hd, log2((double)rope.base)), &sn, &cs);
+  rope.tab[row * rope.stride + i] = make_float2(cs, sn);
+}
+
 template <typename Tin, typename Tout, bool LAYER, int NC>
-__global__ __launch_bounds__(320) void norm_meta_kernel(const Tin* __restrict__ in, const Tout* __restrict__ g,
-                                                        const Tout* __restrict__ b, Tout* __restrict__ out, int H,
-                                                        float eps, MetaChunk c, int* __restrict__ dst,
-                                                        RopeTable rope) {
-  if (threadIdx.x >= 256) {
-    const int i = threadIdx.x - 256, row = (int)blockIdx.x - 1;
-    if (row < 0 || i >= rope.hd / 2) return;
-    const int at = rope.pos_at + row;               // metadata past this chunk is already at dst
-    const int pos = at < META_CHUNK ? c.values[at] : dst[at];
-    float sn, cs;
-    rope_sincos(pos, rope_theta(i, rope.hd, log2((double)rope.base)), &sn, &cs);
-    rope.tab[row * rope.stride + i] = make_float2(cs, sn);
+__global__ __launch_bounds__(norm_rope_threads(NC)) void norm_meta_kernel(
+    const Tin* __restrict__ in, const Tout* __restrict__ g, const Tout* __restrict__ b, Tout* __restrict__ out, int H,
+    float eps, MetaChunk c, int* __restrict__ dst, RopeTable rope) {
+  if (NC < NORM_NC && threadIdx.x >= 256) {
+    if (blockIdx.x > 0) rope_table_row(rope, c, dst, (int)blockIdx.x - 1, threadIdx.x - 256);
     return;
   }
   if (blockIdx.x == 0) {
@@ -166,14 +174,16 @@ __global__ __launch_bounds__(320) void norm_meta_kernel(const Tin* __restrict__ 
     return;
   }
   norm_row<Tin, Tout, LAYER, NC>(in, g, b, out, H, eps, blockIdx.x - 1);
+  if (NC == NORM_NC && rope.tab && threadIdx.x < 64) rope_table_row(rope, c, dst, (int)blockIdx.x - 1, threadIdx.x);
 }
 
 template <typename Tin, typename Tout, bool LAYER, int NC>
 static void norm_launch_nc(const void* in, const void* g, const void* b, void* out, int rows, int H, float eps,
                            hipStream_t s, const MetaChunk* meta, int* meta_dst, const RopeTable& rope) {
   if (meta)
-    hipLaunchKernelGGL((norm_meta_kernel<Tin, Tout, LAYER, NC>), dim3(rows + 1), dim3(rope.tab ? 320 : 256), 0, s,
-                       (const Tin*)in, (const Tout*)g, (const Tout*)b, (Tout*)out, H, eps, *meta, meta_dst, rope);
+    hipLaunchKernelGGL((norm_meta_kernel<Tin, Tout, LAYER, NC>), dim3(rows + 1),
+                       dim3(rope.tab ? norm_rope_threads(NC) : 256), 0, s, (const Tin*)in, (const Tout*)g,
+                       (const Tout*)b, (Tout*)out, H, eps, *meta, meta_dst, rope);
   else
     hipLaunchKernelGGL((norm_kernel<Tin, Tout, LAYER, NC>), dim3(rows), dim3(256), 0, s, (const Tin*)in,
                        (const Tout*)g, (const Tout*)b, (Tout*)out, H, eps);

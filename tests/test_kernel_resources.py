@@ -1,5 +1,5 @@
 """Registers of the built kernels (CPU: the metadata notes of the library's
-gfx950 code objects): no matrix-core matmul or row-attention kernel
+gfx950 code objects): no matrix-core matmul, row-attention or norm kernel
 spills.  (The chunk-attention kernels may set aside a few outside their
 loops.)"""
 import struct
@@ -44,7 +44,8 @@ def test_no_hot_kernel_spills_registers():
     with open(build.LIB, "rb") as f:
         lib = f.read()
     kernels = [k for elf in _code_objects(lib) for k in _kernels(elf)]
-    hot = [k for k in kernels if any(n in k[".name"] for n in ("gemm_ws", "gemm_quad", "gemm_bf16", "attn_rows"))]
+    names = ("gemm_ws", "gemm_quad", "gemm_bf16", "attn_rows", "norm_")
+    hot = [k for k in kernels if any(n in k[".name"] for n in names)]
     assert len(hot) > 100
     spilled = {k[".name"]: (k[".sgpr_spill_count"], k[".vgpr_spill_count"]) for k in hot
                if k[".sgpr_spill_count"] or k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]}
