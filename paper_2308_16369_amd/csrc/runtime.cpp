@@ -170,6 +170,7 @@ struct Plan {
   int C, B, T, row_base, n_pre, n_dec, n_chunks, pre_tiles;
   int qblock;      // chunk rows per chunk-attention q-block (PREFILL_QBLOCK, _SMALL or _F32)
   int pre_slots;   // partial q-block slots of the chunk items (items covering all keys of their rows write O)
+  int n_direct;    // row-attention items that write their row of O (ROW_DIRECT), no partial
   int comb_row0;   // first row whose attention output the combine pass writes
   // row_slot[T] row_pos[T] comb[3T] chunk table [n_chunks][slot, offset, len, first row]
   // pre_work[n_pre][chunk, q_block, partial slot, (first tile << 16) | end tile] dec_work[n_dec]
@@ -337,6 +338,7 @@ Plan make_plan(const sarathi_model_cfg* cfg, const BatchDesc& b) {
   std::vector<int> order;
   for (int r = p.row_base; r < p.T; ++r) order.push_back(r);
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return slot[x] < slot[y]; });
+  p.n_direct = 0;
   for (int r : order) {
     const int ns = (pos[r] + 1 + SPLIT_KEYS - 1) / SPLIT_KEYS;
     // fp32: a row of one split is written by its attention block (no combine;
@@ -345,6 +347,7 @@ Plan make_plan(const sarathi_model_cfg* cfg, const BatchDesc& b) {
     comb[3 * r] = pre_rows + (int)dec.size();
     comb[3 * r + 1] = direct ? 0 : ns;
     comb[3 * r + 2] = 1;
+    p.n_direct += direct;
     for (int s = 0; s < ns; ++s) dec.push_back(((r - p.row_base) << 12) | (direct ? ROW_DIRECT : 0) | s);
   }
   p.n_pre = (int)pre.size() / 4;
@@ -881,8 +884,7 @@ int sarathi_attention_plan(const sarathi_model_cfg* cfg, const sarathi_hybrid_ba
   sarathi_attn_plan o{};
   o.chunk_items = P.n_pre;
   o.decode_items = P.n_dec;
-  long written = P.n_dec;
-  for (int i = 0; i < P.n_dec; ++i) written -= (P.meta[P.o_dec + i] & ROW_DIRECT) != 0;
+  long written = P.n_dec - P.n_direct;   // (contexts past a cache's 2^20 positions reach the flag's bit of an item)
   for (int i = 0; i < P.n_pre; ++i)
     if (pre[4 * i + 2] >= 0) {
       const int len = chunks[4 * pre[4 * i] + 2], q0 = pre[4 * i + 1] * P.qblock;

@@ -319,6 +319,12 @@ def test_attention_plan_counts_partials():
     assert p["partial_rows_read"] == p["partial_rows_written"] and p["combine_rows"] == 101
     with pytest.raises(S.SarathiError):
         S.sarathi_attention_plan(cfg, S.make_batch(-1, 0, 0, [], [])[0])
+    # no cache bounds the contexts of a plan: 2050 and 2049 splits, each a partial row
+    for dtype in (S.BF16, S.F32):
+        cfg = S.make_cfg(hidden=64, n_heads=1, head_dim=64, ffn=128, n_layers=1, dtype=dtype)
+        bb, keep = S.make_batch(-1, 0, 0, [0, 1], [(1 << 20) + 600, 1 << 20])
+        p = S.sarathi_attention_plan(cfg, bb)
+        assert p["partial_rows_written"] == p["partial_rows_read"] == p["decode_items"] == 2050 + 2049
 
 
 def test_attention_plan_invariants_random():
