@@ -1187,7 +1187,15 @@ constexpr WsTile kWsTiles[] = {{64, 64},   {64, 128},  {64, 256},  {96, 128},  {
                                {128, 128}, {128, 192}, {128, 224}, {128, 256}, {160, 128}, {160, 192},
                                {160, 224}, {160, 256}, {288, 192}, {192, 256}, {256, 256}};
 constexpr int kFirstQuadTile = 14;   // the rest run gemm_quad_kernel
-constexpr double kQuadTileUs[] = {1.27, 1.17, 1.5};   // their time per 64-wide k-tile
+// Their price per 64-wide k-tile, and per block beyond the producer tiles' 3 us
+// (us; on the scale of the producer tiles' prices, which run 1-30% above what
+// those measure, most where a round leaves CUs idle).  Fitted to every tile and K-split of the twelve matmuls at 33
+// row counts of 8-1536: the picks then take 1.2% more than the fastest tile, and
+// 1.7% at the loop's own 1.27 / 1.17 / 1.5 without the extra fill (LLaMA-33B
+// layer of 192 rows 364 -> 350 us, 288 rows 406 -> 393, GPT-3 of 400 rows
+// 1648 -> 1619: producer tiles where those took quadrant ones).
+constexpr double kQuadTileUs[] = {1.37, 1.22, 1.56};
+constexpr double kQuadFillUs = 3.5;
 constexpr int kNumWsTiles = sizeof(kWsTiles) / sizeof(kWsTiles[0]);
 
 // Variants of a launch: gemm_ws_kernel with W loaded non-temporally, and
@@ -1269,17 +1277,20 @@ static hipError_t run_ws_f32(int epi, int cfg, const GemmP& p, hipStream_t s) {
 // share the W panel (~4.2 ns when one block streams it alone: every row an
 // HBM miss); a block adds ~3 us of pipeline fill plus its output writes
 // (~40 GB/s per CU); blocks beyond the first 256 run as another round.  The
-// quadrant kernel's k-tiles are priced by measurement.  A
+// quadrant kernel's tiles have prices of their own (above).  A
 // split-K op's reduction pass reads the fp32 partials and writes the result
-// at ~5.5 TB/s.
+// at ~5.5 TB/s.  postproj's takes in the norm that follows, which costs a pass
+// of its own without a split (LLaMA-13B layer of 1024 rows: 614 us with a split
+// 192 x 256, 628 with an unsplit 128 x 192 that runs postproj alone as fast).
 struct WsChoice {
   int cfg, n_split;
   int wide_n = 0;      // quadrant tiles: > 0, that many W panels of them and a tail of narrower tiles
 };
-static WsChoice pick_ws(int M, int N, int K, bool swiglu, int max_split) {
+static WsChoice pick_ws(int M, int N, int K, bool swiglu, bool norm_follows, int max_split) {
   WsChoice best{10, 1};
   double best_t = 1e300;
   const int nk = K / 64;
+  const double norm_us = norm_follows ? 6.0 * (double)M * N / 5.5e6 + 2.0 : 0.0;
   for (int c = 0; c < kNumWsTiles; ++c) {
     const int bm = kWsTiles[c].bm, bn = kWsTiles[c].bn;
     if (bm == 64 && M > 128) continue;   // 64-row tiles only for short batches
@@ -1294,12 +1305,13 @@ static WsChoice pick_ws(int M, int N, int K, bool swiglu, int max_split) {
     const long tiles = (long)tiles_m * ((N + per - 1) / per);
     const double per_k = c >= kFirstQuadTile ? kQuadTileUs[c - kFirstQuadTile]
                                              : 1.9e-3 * bm + (tiles_m >= 2 ? 3.1e-3 : 4.2e-3) * bn;   // us per k-tile
+    const double fill = 3.0 + (c >= kFirstQuadTile ? kQuadFillUs : 0.0);
     for (int ns = 1; ns <= max_split; ++ns) {
       const double rounds = (double)((tiles * ns + 255) / 256);
       const double k_tiles = 2.0 * ((nk / 2 + ns - 1) / ns);               // whole pairs per split
       const double out_bytes = (double)bm * (swiglu ? bn / 2 : bn) * (ns > 1 ? 4.0 : 2.0);
-      double t = rounds * (k_tiles * per_k + 3.0 + out_bytes / 4.0e4);
-      if (ns > 1) t += (ns * 4.0 + 6.0) * (double)M * N / 5.5e6 + 2.0;
+      double t = rounds * (k_tiles * per_k + fill + out_bytes / 4.0e4);
+      t += ns > 1 ? (ns * 4.0 + 6.0) * (double)M * N / 5.5e6 + 2.0 : norm_us;
       if (t < best_t * 0.999) {
         best_t = t;
         best = {c, ns};
@@ -1312,7 +1324,8 @@ static WsChoice pick_ws(int M, int N, int K, bool swiglu, int max_split) {
     const int pert = per / 4 * QUAD_TAIL, left = N - wide_n * per;
     if (left <= 0 || (long)tiles_m * ((left + pert - 1) / pert) > 256) continue;
     const double out_us = (double)bm * per * 2.0 / 4.0e4;
-    const double t = rounds * (nk * per_k + 3.0 + out_us) + nk * (bm == 256 ? 1.15 : 0.95) + 3.0 + out_us * 0.75;
+    const double tail_us = nk * (bm == 256 ? 1.15 : 0.95) + fill + out_us * 0.75;
+    const double t = rounds * (nk * per_k + fill + out_us) + tail_us + norm_us;
     if (t < best_t * 0.999) {
       best_t = t;
       best = {c, 1, wide_n};
@@ -1459,7 +1472,7 @@ hipError_t launch_linear(int dtype, const LinearArgs& a, hipStream_t s, int forc
   }
   int cfg, BM, BN, ws_split = 1, wide_n = 0;
   if (ws) {
-    WsChoice ch = pick_ws(a.M, a.N, a.K, swiglu, max_split);
+    WsChoice ch = pick_ws(a.M, a.N, a.K, swiglu, a.kind == LIN_RESID, max_split);
     if (force_tile >= 0 && force_tile < kNumWsTiles) ch = {force_tile, std::min(std::max(force_split, 1), max_split)};
     cfg = ch.cfg;
     ws_split = ch.n_split;

@@ -380,3 +380,19 @@ def test_attention_plan_block_size():
     p = S.sarathi_attention_plan(cfg, bb)
     assert p["chunk_items"] == 4
     assert p["partial_rows_written"] == 2 * 512 and p["combine_rows"] == 512
+
+
+def test_linear_plan_part_grids():
+    """Residual ops whose quadrant tiles would leave CUs idle or pay six
+    splits run producer/consumer tiles, which measure faster there; a
+    postproj whose split costs no time takes it (its norm then needs no pass)."""
+    from paper_2308_16369_amd import sarathi as S
+    quad = {(288, 192), (192, 256), (256, 256)}
+    # LLaMA-33B ffn_ln2 (192 x 256 in six splits 77 us, 128 x 224 in four 68; 288 x 192 89, 160 x 224 85), LLaMA-13B
+    # and LLaMA-33B postproj (192 x 256 in six or four splits 38 and 49, 128 x 256 in four or three 34 and 46)
+    for kind, M, N, K in ((S.LINEAR_RESID_F32IN, 176, 6656, 17920), (S.LINEAR_RESID_F32IN, 288, 6656, 17920),
+                          (S.LINEAR_RESID, 352, 5120, 5120), (S.LINEAR_RESID, 352, 6656, 6656)):
+        assert S.sarathi_linear_plan(S.BF16, kind, M, N, K, 24 * min(M, 512) * N)[:2] not in quad
+    # GPT-3 ffn_ln1: two 288-row M-tiles pad 448 rows to 576 (562 us against 519)
+    assert S.sarathi_linear_plan(S.BF16, S.LINEAR_GELU, 448, 49152, 12288, 0)[:2] == (160, 192)
+    assert S.sarathi_linear_plan(S.BF16, S.LINEAR_RESID, 1024, 5120, 5120, 24 * 512 * 5120)[2] > 1
