@@ -340,9 +340,14 @@ int sarathi_linear(int dtype, int kind, int M, int N, int K, const void* x, cons
  * bytes written, then read back) are traffic beyond the method's own.
  * Errors: EINVAL (NULL outputs, bad kind or sizes), EUNSUPPORTED (dtype,
  * K not a multiple of 8).
+ * The same op's tail: where whole rounds of the plan's blocks leave part of
+ * the last round idle, the last *tail_cols output columns run as blocks of
+ * *tail_bn rows of W in the same launch (0, 0: every block is *bm x *bn).
  */
 int sarathi_linear_plan(int dtype, int kind, int M, int N, int K, size_t scratch_bytes, int* bm, int* bn,
                         int* n_split);
+int sarathi_linear_plan_tail(int dtype, int kind, int M, int N, int K, size_t scratch_bytes, int* tail_cols,
+                             int* tail_bn);
 size_t sarathi_layer_split_scratch_bytes(const sarathi_model_cfg* cfg, int n_tokens);
 
 /*

@@ -402,31 +402,37 @@ def tile_sweep(shape, T: int, iters: int = 20) -> List[dict]:
         resid = torch.randn(T, N, generator=g, device="cuda").to(resid_dt)
         y = torch.empty(T, N, dtype=out_dt, device="cuda")
         pick = S.sarathi_linear_plan(S.BF16, kind, T, N, K, scratch_bytes)
+        tail = S.sarathi_linear_plan_tail(S.BF16, kind, T, N, K, scratch_bytes)
+        planned = lambda: S.sarathi_linear(S.BF16, kind, T, N, K, x.data_ptr(), w.data_ptr(), resid.data_ptr(),
+                                           y.data_ptr(), scratch.data_ptr(), scratch_bytes)
         splits = sorted({1, pick[2]}) if kind in (S.LINEAR_RESID, S.LINEAR_RESID_F32IN) else [1]
         if K % 64 != 0:
             # no tile choice for a K off the 64-wide k-tiles: the op's one kernel, as the planner runs it
-            run = lambda: S.sarathi_linear(S.BF16, kind, T, N, K, x.data_ptr(), w.data_ptr(), resid.data_ptr(),
-                                           y.data_ptr(), scratch.data_ptr(), scratch_bytes)
             for _ in range(3):
-                run()
-            ms = _time(run, iters)
+                planned()
+            ms = _time(planned, iters)
             out.append({"op": name, "T": T, "N": N, "K": K, "bm": pick[0], "bn": pick[1], "n_split": pick[2],
-                        "us": ms * 1e3, "tflops": 2.0 * T * w_rows * K / (ms * 1e-3) / 1e12, "picked": True})
+                        "tail_cols": tail[0], "tail_bn": tail[1], "us": ms * 1e3,
+                        "tflops": 2.0 * T * w_rows * K / (ms * 1e-3) / 1e12, "picked": True})
             del x, w, resid, y
             continue
         for tile in range(S.sarathi_linear_tile_count()):
             bm, bn = S.sarathi_linear_tile_shape(tile)
             if bm == 64 and T > 128:    # the planner takes 64-row tiles up to 128 rows
                 continue
+            forced = lambda: S.sarathi_linear_tiled(kind, T, N, K, x.data_ptr(), w.data_ptr(), resid.data_ptr(),
+                                                    y.data_ptr(), scratch.data_ptr(), scratch_bytes, tile, ns)
             for ns in splits:
-                run = lambda: S.sarathi_linear_tiled(kind, T, N, K, x.data_ptr(), w.data_ptr(), resid.data_ptr(),
-                                                     y.data_ptr(), scratch.data_ptr(), scratch_bytes, tile, ns)
-                for _ in range(3):
-                    run()
-                ms = _time(run, iters)
-                out.append({"op": name, "T": T, "N": N, "K": K, "bm": bm, "bn": bn, "n_split": ns, "us": ms * 1e3,
-                            "tflops": 2.0 * T * w_rows * K / (ms * 1e-3) / 1e12,
-                            "picked": (bm, bn, ns) == tuple(pick)})
+                # a given tile runs without a tail: the pick that has one is timed as planned, in a row of its own
+                is_pick = (bm, bn, ns) == tuple(pick)
+                for run, cols in ([(forced, 0), (planned, tail[0])] if is_pick and tail[0] else [(forced, 0)]):
+                    for _ in range(3):
+                        run()
+                    ms = _time(run, iters)
+                    out.append({"op": name, "T": T, "N": N, "K": K, "bm": bm, "bn": bn, "n_split": ns,
+                                "tail_cols": cols, "tail_bn": tail[1] if cols else 0, "us": ms * 1e3,
+                                "tflops": 2.0 * T * w_rows * K / (ms * 1e-3) / 1e12,
+                                "picked": is_pick and cols == tail[0]})
         del x, w, resid, y
     return out
 
@@ -436,12 +442,14 @@ def tile_sweep_markdown(workload: str, rows: List[dict]) -> str:
              "Each op alone through `sarathi_linear_tiled` (split-K reductions included), mean of 20 calls after "
              "3 warm-ups; weights re-read every call (a 256 MB memory-side cache can hold one "
              "op's weights between calls, so these times can be below the in-layer ones); preproj without its "
-             "RoPE + KV-append epilogue.  * = the planner's pick.\n",
+             "RoPE + KV-append epilogue.  * = the planner's pick; a tail = the last columns run as narrower tiles "
+             "in the same launch.\n",
              "| op | N x K | tile (BM x BN) | K-splits | us | TFLOP/s | |", "|---|---|---|---|---|---|---|"]
     for e in rows:
         mark = "*" if e["picked"] else ""
-        lines.append(f"| {e['op']} | {e['N']} x {e['K']} | {e['bm']} x {e['bn']} | {e['n_split']} | {e['us']:.1f} | "
-                     f"{e['tflops']:.0f} | {mark} |")
+        tail = f", tail {e['tail_cols']} x {e['tail_bn']}" if e["tail_cols"] else ""
+        lines.append(f"| {e['op']} | {e['N']} x {e['K']} | {e['bm']} x {e['bn']}{tail} | {e['n_split']} | "
+                     f"{e['us']:.1f} | {e['tflops']:.0f} | {mark} |")
     return "\n".join(lines) + "\n"
 
 

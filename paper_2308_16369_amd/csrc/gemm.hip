@@ -1370,7 +1370,7 @@ bool linear_tile_shape(int tile, int* bm, int* bn) {
 
 hipError_t launch_linear(int dtype, const LinearArgs& a, hipStream_t s, int force_tile, int force_split,
                          LinearPlan* plan) {
-  if (plan) *plan = LinearPlan{0, 0, 0};
+  if (plan) *plan = LinearPlan{};
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   GemmP p{};
   p.A = a.x; p.W = a.w; p.M = a.M; p.N = a.N; p.K = a.K;
@@ -1407,7 +1407,7 @@ hipError_t launch_linear(int dtype, const LinearArgs& a, hipStream_t s, int forc
       p.n_split = (a.K + p.k_split - 1) / p.k_split;
     }
     if (plan) {
-      *plan = LinearPlan{bm, bn, p.n_split};
+      *plan = LinearPlan{bm, bn, p.n_split, 0, 0};
       return hipSuccess;
     }
     const bool split = p.n_split > 1;
@@ -1548,7 +1548,7 @@ hipError_t launch_linear(int dtype, const LinearArgs& a, hipStream_t s, int forc
     p.rotate_k = (ws && cfg < kFirstQuadTile && p.tiles_m == 2 && nk_block <= 192) ? 1 : 0;
   }
   if (plan) {
-    *plan = LinearPlan{BM, BN, p.n_split};
+    *plan = LinearPlan{BM, BN, p.n_split, wide_n > 0 ? a.N - p.tail_n0 : 0, wide_n > 0 ? BN / 4 * QUAD_TAIL : 0};
     return hipSuccess;
   }
   hipError_t e;

@@ -97,9 +97,10 @@ constexpr int MAX_SPLIT = 6;   // split-K partials: at most MAX_SPLIT x [M, N] f
 // shape with force_split K-splits (residual kinds with scratch) instead of the
 // cost model's choice.
 // With plan non-null nothing is launched: *plan receives the block shape and
-// K-split count the op would run with.
+// K-split count the op would run with, and the output columns left to narrower
+// tail tiles (of tail_bn W rows; 0: none).
 struct LinearPlan {
-  int bm, bn, n_split;
+  int bm, bn, n_split, tail_cols, tail_bn;
 };
 hipError_t launch_linear(int dtype, const LinearArgs& a, hipStream_t s, int force_tile = -1, int force_split = 0,
                          LinearPlan* plan = nullptr);

@@ -900,9 +900,8 @@ int sarathi_attention_plan(const sarathi_model_cfg* cfg, const sarathi_hybrid_ba
   return SARATHI_OK;
 }
 
-int sarathi_linear_plan(int dtype, int kind, int M, int N, int K, size_t scratch_bytes, int* bm, int* bn,
-                        int* n_split) {
-  if (!bm || !bn || !n_split) return fail(SARATHI_EINVAL, "NULL pointer");
+namespace {
+int linear_plan(int dtype, int kind, int M, int N, int K, size_t scratch_bytes, LinearPlan* pl) {
   if (dtype != SARATHI_F32 && dtype != SARATHI_BF16) return fail(SARATHI_EUNSUPPORTED, "dtype %d", dtype);
   if (kind < SARATHI_LINEAR_PLAIN || kind > SARATHI_LINEAR_GELU) return fail(SARATHI_EINVAL, "kind %d", kind);
   if (M < 1 || N < 1 || K < 1) return fail(SARATHI_EINVAL, "M, N, K must be positive");
@@ -914,9 +913,28 @@ int sarathi_linear_plan(int dtype, int kind, int M, int N, int K, size_t scratch
     a.parts = &dummy;
     a.parts_cap = scratch_bytes / 4;
   }
+  if (launch_linear(dtype, a, nullptr, -1, 0, pl) != hipSuccess) return fail(SARATHI_EINVAL, "no plan for this op");
+  return SARATHI_OK;
+}
+}  // namespace
+
+int sarathi_linear_plan(int dtype, int kind, int M, int N, int K, size_t scratch_bytes, int* bm, int* bn,
+                        int* n_split) {
+  if (!bm || !bn || !n_split) return fail(SARATHI_EINVAL, "NULL pointer");
   LinearPlan pl{};
-  if (launch_linear(dtype, a, nullptr, -1, 0, &pl) != hipSuccess) return fail(SARATHI_EINVAL, "no plan for this op");
+  const int rc = linear_plan(dtype, kind, M, N, K, scratch_bytes, &pl);
+  if (rc) return rc;
   *bm = pl.bm; *bn = pl.bn; *n_split = pl.n_split;
+  return SARATHI_OK;
+}
+
+int sarathi_linear_plan_tail(int dtype, int kind, int M, int N, int K, size_t scratch_bytes, int* tail_cols,
+                             int* tail_bn) {
+  if (!tail_cols || !tail_bn) return fail(SARATHI_EINVAL, "NULL pointer");
+  LinearPlan pl{};
+  const int rc = linear_plan(dtype, kind, M, N, K, scratch_bytes, &pl);
+  if (rc) return rc;
+  *tail_cols = pl.tail_cols; *tail_bn = pl.tail_bn;
   return SARATHI_OK;
 }
 

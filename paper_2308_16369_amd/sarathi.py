@@ -133,6 +133,8 @@ EXPORTS = {
                                           ct.POINTER(sarathi_attn_plan)]),
     "sarathi_linear_plan": (ct.c_int, [ct.c_int, ct.c_int, ct.c_int, ct.c_int, ct.c_int, ct.c_size_t,
                                        ct.POINTER(ct.c_int), ct.POINTER(ct.c_int), ct.POINTER(ct.c_int)]),
+    "sarathi_linear_plan_tail": (ct.c_int, [ct.c_int, ct.c_int, ct.c_int, ct.c_int, ct.c_int, ct.c_size_t,
+                                            ct.POINTER(ct.c_int), ct.POINTER(ct.c_int)]),
     "sarathi_layer_split_scratch_bytes": (ct.c_size_t, [ct.POINTER(sarathi_model_cfg), ct.c_int]),
     "sarathi_linear_tile_count": (ct.c_int, []),
     "sarathi_linear_tile_shape": (ct.c_int, [ct.c_int, ct.POINTER(ct.c_int), ct.POINTER(ct.c_int)]),
@@ -352,6 +354,13 @@ def sarathi_linear_plan(dtype, kind, M, N, K, scratch_bytes: int = 0):
     bm, bn, ns = ct.c_int(), ct.c_int(), ct.c_int()
     _check(lib().sarathi_linear_plan(dtype, kind, M, N, K, scratch_bytes, ct.byref(bm), ct.byref(bn), ct.byref(ns)))
     return bm.value, bn.value, ns.value
+
+
+def sarathi_linear_plan_tail(dtype, kind, M, N, K, scratch_bytes: int = 0):
+    """(columns, W rows per block) of the narrower tiles that end the op; (0, 0) where it has none."""
+    cols, bn = ct.c_int(), ct.c_int()
+    _check(lib().sarathi_linear_plan_tail(dtype, kind, M, N, K, scratch_bytes, ct.byref(cols), ct.byref(bn)))
+    return cols.value, bn.value
 
 
 def sarathi_layer_split_scratch_bytes(cfg: sarathi_model_cfg, n_tokens: int) -> int:

@@ -296,6 +296,13 @@ def test_linear_plan_reports_split_choice():
     assert S.sarathi_linear_plan(S.BF16, S.LINEAR_PLAIN, 320, 15360, 5120, scratch)[2] == 1
     with pytest.raises(S.SarathiError):
         S.sarathi_linear_plan(S.BF16, 9, 320, 5120, 5120, 0)
+    # 432 blocks of 256 x 256 are 1.69 rounds: 256 of them, then 192-wide tiles over the columns left
+    assert S.sarathi_linear_plan(S.BF16, S.LINEAR_SWIGLU, 1021, 13824, 5120, 0) == (256, 256, 1)
+    assert S.sarathi_linear_plan_tail(S.BF16, S.LINEAR_SWIGLU, 1021, 13824, 5120, 0) == (13824 - 64 * 128, 192)
+    assert S.sarathi_linear_plan_tail(S.BF16, S.LINEAR_PLAIN, 320, 15360, 5120, 0) == (0, 0)
+    assert S.sarathi_linear_plan_tail(S.F32, S.LINEAR_PLAIN, 1021, 15360, 5120, 0) == (0, 0)
+    with pytest.raises(S.SarathiError):
+        S.sarathi_linear_plan_tail(S.BF16, 9, 320, 5120, 5120, 0)
 
 
 def test_attention_plan_counts_partials():

@@ -44,3 +44,15 @@ def test_tile_sweep_tiny():
     assert [e["picked"] for e in rows if e["op"] == "ffn_ln2"] == [True]
     md = ablation.tile_sweep_markdown("tiny", rows)
     assert md.count("\n|") == len(rows) + 2
+
+
+def test_tile_sweep_marks_the_planned_launch():
+    """An op that ends in narrower tiles: its pick is the row timed as planned,
+    and the given tile's own row (without a tail) is not."""
+    shape = wl.LayerShape(hidden=1024, n_heads=8, head_dim=128, ffn=13824, dtype="bf16")
+    rows = [e for e in ablation.tile_sweep(shape, 1021, iters=2) if e["op"] == "ffn_ln1"]
+    picked = [e for e in rows if e["picked"]]
+    assert len(picked) == 1 and 0 < picked[0]["tail_cols"] < 13824 and picked[0]["tail_bn"] == 192
+    same = [e["tail_cols"] for e in rows if (e["bm"], e["bn"]) == (picked[0]["bm"], picked[0]["bn"])]
+    assert sorted(same) == [0, picked[0]["tail_cols"]]
+    assert f"tail {picked[0]['tail_cols']} x 192" in ablation.tile_sweep_markdown("tail", rows)

@@ -84,23 +84,36 @@ def test_f32_tile_edges(mnk):
 
 @pytest.mark.parametrize("kind,M,N,K", [(S.LINEAR_SWIGLU, 1021, 13824, 1024), (S.LINEAR_SWIGLU, 544, 17920, 1024),
                                         (S.LINEAR_SWIGLU, 1021, 13826, 1024), (S.LINEAR_PLAIN, 1021, 27648, 512),
-                                        (S.LINEAR_GELU, 1000, 27660, 512)])
+                                        (S.LINEAR_GELU, 1000, 27660, 512), (S.LINEAR_RESID, 1021, 27648, 512),
+                                        (S.LINEAR_RESID, 544, 35842, 512), (S.LINEAR_RESID_F32IN, 1000, 27661, 512),
+                                        (S.LINEAR_RESID_F32IN, 544, 35840, 512)])
 def test_quad_tail(kind, M, N, K):
     """Shapes whose 256-wide tiles fill one round and a part of the next: the columns left go to 192-wide tiles
-    (a last tile that N cuts, N no multiple of 8)."""
+    (a last tile that N cuts, N no multiple of 8 or of 4), with every epilogue but the rotary one (below); the
+    residual kinds without scratch, so unsplit."""
     assert S.sarathi_linear_plan(S.BF16, kind, M, N, K, 0)[1] == 256
+    tail_cols, tail_bn = S.sarathi_linear_plan_tail(S.BF16, kind, M, N, K, 0)
+    assert 0 < tail_cols < N and tail_bn == 192
     g = torch.Generator(device="cuda").manual_seed(M + N)
     x = torch.empty(M, K, device="cuda").normal_(generator=g).bfloat16()
     w = torch.empty(2 * N if kind == S.LINEAR_SWIGLU else N, K, device="cuda").normal_(0, 0.05, generator=g).bfloat16()
-    out = torch.full((M, N), float("nan"), device="cuda", dtype=torch.bfloat16)
-    S.sarathi_linear(S.BF16, kind, M, N, K, x.data_ptr(), w.data_ptr(), 0, out.data_ptr(), 0, 0,
-                     torch.cuda.current_stream().cuda_stream)
+    resid = None
+    if kind in (S.LINEAR_RESID, S.LINEAR_RESID_F32IN):
+        resid = torch.empty(M, N, device="cuda").normal_(generator=g)
+        if kind == S.LINEAR_RESID:
+            resid = resid.bfloat16()
+    out = torch.full((M, N), float("nan"), device="cuda",
+                     dtype=torch.float32 if kind == S.LINEAR_RESID else torch.bfloat16)
+    S.sarathi_linear(S.BF16, kind, M, N, K, x.data_ptr(), w.data_ptr(), 0 if resid is None else resid.data_ptr(),
+                     out.data_ptr(), 0, 0, torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     z = x.double() @ w.double().t()
     if kind == S.LINEAR_SWIGLU:
         z = torch.nn.functional.silu(z[:, :N]) * z[:, N:]
     elif kind == S.LINEAR_GELU:
         z = torch.nn.functional.gelu(z)
+    elif resid is not None:
+        z += resid.double()
     assert _err(out, z.cpu()) <= 1e-2
 
 
@@ -111,6 +124,7 @@ def test_quad_tail_rope_layer():
     import workloads as wl
     from test_gpu_parity import run_and_check
     assert S.sarathi_linear_plan(S.BF16, S.LINEAR_PLAIN, 1021, 3 * 72 * 128, 512, 0)[:2] == (256, 256)
+    assert S.sarathi_linear_plan_tail(S.BF16, S.LINEAR_PLAIN, 1021, 3 * 72 * 128, 512, 0) == (11264, 192)
     shape = wl.LayerShape(hidden=512, n_heads=72, head_dim=128, ffn=4096, dtype="bf16")
     b = wl.Batch(prefill_slot=0, chunk_offset=17, chunk_len=1000, decode_slots=np.arange(1, 22, dtype=np.int32),
                  decode_ctx=np.array([(53 * i) % 1000 for i in range(1, 22)], np.int32))
