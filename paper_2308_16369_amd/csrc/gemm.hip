@@ -1296,9 +1296,8 @@ static WsChoice pick_ws(int M, int N, int K, bool swiglu, bool norm_follows, int
     if (bm == 64 && M > 128) continue;   // 64-row tiles only for short batches
     // 128-row tiles: two cover 256 rows where 160-row ones pad to 320 (LLaMA-13B
     // at 256 rows, alone: preproj 55.7 -> 52.4 us, ffn_ln1 84.2 -> 77.2, ffn_ln2
-    // 51.0 -> 49.2).  K below 1024 keeps the picks that the tile tests pin
-    // (200 x 19968 x 512 would gain 1.2 of 13.4 us).
-    if (bm == 128 && (M <= 96 || K < 1024)) continue;
+    // 51.0 -> 49.2; 200 x 15360 x 512 10.7 -> 9.6, 200 x 19968 x 960 18.8 -> 17.1).
+    if (bm == 128 && M <= 96) continue;
     if (c >= kFirstQuadTile && M <= 160) continue;
     const int per = swiglu ? bn / 2 : bn;
     const int tiles_m = (M + bm - 1) / bm;

@@ -117,15 +117,16 @@ def test_quad_tail(kind, M, N, K):
     assert _err(out, z.cpu()) <= 1e-2
 
 
-def test_quad_tail_rope_layer():
-    """The fused rotary + KV-append epilogue over wide tiles and a tail: 72 heads, 1021 rows."""
+@pytest.mark.parametrize("nh,T,tile,tail", [(72, 1021, (256, 256), (11264, 192)), (73, 700, (192, 256), (11648, 192))])
+def test_quad_tail_rope_layer(nh, T, tile, tail):
+    """The fused rotary + KV-append epilogue over wide tiles and a tail."""
     import numpy as np
 
     import workloads as wl
     from test_gpu_parity import run_and_check
-    assert S.sarathi_linear_plan(S.BF16, S.LINEAR_PLAIN, 1021, 3 * 72 * 128, 512, 0)[:2] == (256, 256)
-    assert S.sarathi_linear_plan_tail(S.BF16, S.LINEAR_PLAIN, 1021, 3 * 72 * 128, 512, 0) == (11264, 192)
-    shape = wl.LayerShape(hidden=512, n_heads=72, head_dim=128, ffn=4096, dtype="bf16")
-    b = wl.Batch(prefill_slot=0, chunk_offset=17, chunk_len=1000, decode_slots=np.arange(1, 22, dtype=np.int32),
+    assert S.sarathi_linear_plan(S.BF16, S.LINEAR_PLAIN, T, 3 * nh * 128, 512, 0)[:2] == tile
+    assert S.sarathi_linear_plan_tail(S.BF16, S.LINEAR_PLAIN, T, 3 * nh * 128, 512, 0) == tail
+    shape = wl.LayerShape(hidden=512, n_heads=nh, head_dim=128, ffn=4096, dtype="bf16")
+    b = wl.Batch(prefill_slot=0, chunk_offset=17, chunk_len=T - 21, decode_slots=np.arange(1, 22, dtype=np.int32),
                  decode_ctx=np.array([(53 * i) % 1000 for i in range(1, 22)], np.int32))
-    run_and_check(wl.make_instance(shape, b, max_seq_len=1024, n_slots=22, seed=29), "rope tail T=1021")
+    run_and_check(wl.make_instance(shape, b, max_seq_len=1024, n_slots=22, seed=29), f"rope tail T={T}")

@@ -245,28 +245,38 @@ def test_layer_head_dim_128_tiny_bf16():
 
 
 # (heads, head_dim, chunk rows, decodes, preproj tile the planner picks): the
-# fused RoPE + KV-append epilogue on every producer/consumer tile width,
-# including tiles that cut heads (BN 192 and 224 against 128-wide heads) and
-# a ragged last column tile
-ROPE_TILES = [(40, 128, 4, 4, (64, 64)), (52, 128, 5, 3, (64, 128)), (52, 128, 66, 4, (96, 128)),
-              (52, 128, 96, 4, (96, 192)), (52, 128, 190, 10, (160, 192)), (52, 128, 330, 10, (160, 256)),
-              (52, 128, 790, 10, (160, 224)), (104, 64, 790, 10, (160, 224))]
+# fused RoPE + KV-append epilogue on every tile of both matmul kernels,
+# including tiles that cut heads (BN 192 and 224 against 128-wide heads),
+# ragged last column tiles and partial M-tiles
+ROPE_TILES = [(40, 128, 4, 4, (64, 64)), (52, 128, 5, 3, (64, 128)), (129, 128, 4, 4, (64, 256)),
+              (52, 128, 66, 4, (96, 128)),
+              (88, 128, 4, 4, (96, 192)), (77, 128, 157, 4, (96, 256)), (53, 128, 96, 4, (128, 128)),
+              (52, 128, 190, 10, (128, 192)), (72, 128, 157, 4, (128, 224)), (52, 128, 330, 10, (128, 256)),
+              (33, 128, 253, 4, (160, 128)), (45, 128, 253, 4, (160, 192)), (52, 128, 790, 10, (160, 224)),
+              (104, 64, 790, 10, (160, 224)), (77, 128, 253, 4, (160, 256)), (89, 128, 196, 4, (288, 192)),
+              (177, 64, 191, 9, (288, 192)), (89, 128, 157, 4, (192, 256)), (69, 128, 396, 4, (256, 256))]
 
 
 @pytest.mark.parametrize("nh,hd,C,B,tile", ROPE_TILES)
 def test_layer_rope_epilogue_every_tile(nh, hd, C, B, tile):
     """q, k_new and v_new from preproj's fused rotary + KV-append epilogue
     against the oracle, on wide-QKV layers whose row counts make the planner
-    pick each tile shape."""
+    pick each tile shape (the quadrant tiles without a tail of narrower ones)."""
     # the FFN about as wide as the attention output, so that y - hres (the FFN
     # output) is not small beside the error that postproj's long sum puts on h
-    shape = _tiny_shape("bf16", hidden=512, n_heads=nh, head_dim=hd, ffn=4096)
+    shape = _tiny_shape("bf16", hidden=512, n_heads=nh, head_dim=hd, ffn=max(4096, nh * hd))
     T = C + B
     assert tuple(S.sarathi_linear_plan(S.BF16, S.LINEAR_PLAIN, T, 3 * nh * hd, 512, 0)[:2]) == tile
+    assert S.sarathi_linear_plan_tail(S.BF16, S.LINEAR_PLAIN, T, 3 * nh * hd, 512, 0) == (0, 0)
     b = wl.Batch(prefill_slot=0, chunk_offset=17, chunk_len=C, decode_slots=np.arange(1, B + 1, dtype=np.int32),
                  decode_ctx=np.array([(53 * i) % 1000 for i in range(1, B + 1)], np.int32))
     run_and_check(wl.make_instance(shape, b, max_seq_len=1024, n_slots=B + 1, seed=23),
                   f"rope epilogue nh={nh} hd={hd} T={T} tile={tile}")
+
+
+def test_rope_tiles_are_every_tile():
+    tiles = {S.sarathi_linear_tile_shape(t) for t in range(S.sarathi_linear_tile_count())}
+    assert {case[4] for case in ROPE_TILES} == tiles
 
 
 @pytest.mark.parametrize("dtype,hidden,norm", [("bf16", 24576, "rms"), ("bf16", 12296, "layer"), ("bf16", 4104, "rms"),
