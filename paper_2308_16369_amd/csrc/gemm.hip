@@ -1281,7 +1281,9 @@ static hipError_t run_ws_f32(int epi, int cfg, const GemmP& p, hipStream_t s) {
 // split-K op's reduction pass reads the fp32 partials and writes the result
 // at ~5.5 TB/s.  postproj's takes in the norm that follows, which costs a pass
 // of its own without a split (LLaMA-13B layer of 1024 rows: 614 us with a split
-// 192 x 256, 628 with an unsplit 128 x 192 that runs postproj alone as fast).
+// 192 x 256, 628 with an unsplit 128 x 192 that runs postproj alone as fast);
+// the pass counts by its traffic, without its launch, so that a small op called
+// alone is not split for it (200 x 5120 x 704: 11.0 us, 13.2 in two splits).
 struct WsChoice {
   int cfg, n_split;
   int wide_n = 0;      // quadrant tiles: > 0, that many W panels of them and a tail of narrower tiles
@@ -1290,7 +1292,7 @@ static WsChoice pick_ws(int M, int N, int K, bool swiglu, bool norm_follows, int
   WsChoice best{10, 1};
   double best_t = 1e300;
   const int nk = K / 64;
-  const double norm_us = norm_follows ? 6.0 * (double)M * N / 5.5e6 + 2.0 : 0.0;
+  const double norm_us = norm_follows ? 6.0 * (double)M * N / 5.5e6 : 0.0;
   for (int c = 0; c < kNumWsTiles; ++c) {
     const int bm = kWsTiles[c].bm, bn = kWsTiles[c].bn;
     if (bm == 64 && M > 128) continue;   // 64-row tiles only for short batches
