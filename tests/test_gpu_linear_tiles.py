@@ -1,7 +1,8 @@
 """Edges of the linear ops' matrix-core kernels through the C-ABI: the large
 bf16 tiles (192 x 256 and 256 x 256) at one to three k-tiles, rows around the
 tile height, column counts that are no multiple of four and an output that is
-not 16-byte aligned; the fp32 tiles at K tails and partial tiles.
+not 16-byte aligned; every fp32 tile at K tails and partial tiles, split and
+unsplit.
 
 Tolerances: bf16 results are one rounding (2^-9) from an fp32 sum whose terms
 the test keeps at |x w| <= ~0.5, so 1e-2 of the largest output; fp32 sums of K
@@ -80,6 +81,63 @@ def test_f32_tile_edges(mnk):
                              torch.cuda.current_stream().cuda_stream)
             torch.cuda.synchronize()
             assert _err(out, _ref(kind, x, w, resid, N)) <= 2e-5, (kind, scratch_bytes)
+
+
+# (M, N, K, fp32 tile the planner picks): every fp32 tile with a partial M-tile, a partial panel and a short last
+# k-tile (K % 32 = 8), two k-tiles (fewer than the ring's stages) and nine (more)
+F32_PLAIN = [(5, 33, 40, (32, 32)), (5, 33, 264, (32, 32)), (5, 8201, 40, (32, 64)), (5, 8201, 264, (32, 64)),
+             (33, 8201, 40, (64, 64)), (33, 8201, 264, (64, 64)), (65, 8201, 40, (96, 64)), (65, 8201, 264, (96, 64)),
+             (97, 8201, 40, (160, 64)), (129, 12001, 264, (160, 64)), (161, 12001, 40, (96, 128)),
+             (161, 12001, 264, (96, 128)), (321, 8201, 40, (160, 128)), (290, 15001, 264, (160, 128))]
+F32_SWIGLU = [(5, 33, 40, (32, 32)), (5, 33, 264, (32, 32)), (5, 4101, 40, (32, 64)), (5, 4101, 264, (32, 64)),
+              (33, 4101, 40, (64, 64)), (33, 4101, 264, (64, 64)), (65, 4101, 40, (96, 64)), (65, 4101, 264, (96, 64)),
+              (97, 4101, 40, (160, 64)), (129, 6150, 264, (160, 64)), (65, 8201, 40, (96, 128)),
+              (65, 8201, 264, (96, 128)), (129, 8201, 40, (160, 128)), (129, 8201, 264, (160, 128))]
+# split over K, the last split short
+F32_SPLIT = [(5, 33, 2056, (32, 32)), (5, 2062, 2056, (32, 64)), (33, 2062, 2056, (64, 64)), (65, 2062, 2056, (96, 64)),
+             (129, 2062, 2056, (160, 64)), (65, 6150, 2056, (96, 128)), (129, 6150, 2056, (160, 128))]
+
+
+@pytest.mark.parametrize("kind,split,M,N,K,tile", [
+    (kind, split, *case)
+    for kinds, split, cases in (([k for k in KINDS if k != S.LINEAR_SWIGLU], False, F32_PLAIN),
+                                ([S.LINEAR_SWIGLU], False, F32_SWIGLU),
+                                ([S.LINEAR_RESID, S.LINEAR_RESID_F32IN], True, F32_SPLIT))
+    for kind in kinds for case in cases])
+def test_f32_every_tile(kind, split, M, N, K, tile):
+    scratch = torch.empty(S.sarathi_linear_scratch_bytes(M, N) if split else 0, dtype=torch.uint8, device="cuda")
+    plan = S.sarathi_linear_plan(S.F32, kind, M, N, K, scratch.numel())
+    assert plan[:2] == tile and (plan[2] > 1) == split
+    x, w, resid = _inputs(kind, M, N, K, torch.float32, M + N + K + kind)
+    xd = torch.cat([x.flatten(), torch.full((64,), float("nan"))]).cuda()
+    wd = torch.cat([w.flatten(), torch.full((64,), float("nan"))]).cuda()
+    rd = None if resid is None else resid.cuda()
+    buf = torch.full((M * N + 64,), 7.0, dtype=torch.float32, device="cuda")
+    out = buf[:M * N]
+    S.sarathi_linear(S.F32, kind, M, N, K, xd.data_ptr(), wd.data_ptr(), 0 if rd is None else rd.data_ptr(),
+                     out.data_ptr(), scratch.data_ptr() if split else 0, scratch.numel(),
+                     torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert _err(out.view(M, N), _ref(kind, x, w, resid, N)) <= 2e-5
+    assert bool((buf[M * N:] == 7.0).all())
+
+
+# (hidden, heads, head_dim, rows, preproj tile): the rotary + KV-append epilogue on every fp32 tile, hidden no
+# multiple of 32
+@pytest.mark.parametrize("H,nh,hd,T,tile", [(264, 1, 64, 5, (32, 32)), (264, 43, 64, 5, (32, 64)),
+                                            (264, 43, 64, 33, (64, 64)), (264, 43, 64, 65, (96, 64)),
+                                            (264, 57, 64, 129, (160, 64)), (264, 57, 64, 161, (96, 128)),
+                                            (264, 57, 128, 129, (160, 128))])
+def test_f32_rope_every_tile(H, nh, hd, T, tile):
+    import numpy as np
+
+    import workloads as wl
+    from test_gpu_parity import run_and_check
+    assert S.sarathi_linear_plan(S.F32, S.LINEAR_PLAIN, T, 3 * nh * hd, H, 0)[:2] == tile
+    shape = wl.LayerShape(hidden=H, n_heads=nh, head_dim=hd, ffn=1024, dtype="f32")
+    b = wl.Batch(prefill_slot=0, chunk_offset=17, chunk_len=T - 2, decode_slots=np.array([1, 2], np.int32),
+                 decode_ctx=np.array([3, 190], np.int32))
+    run_and_check(wl.make_instance(shape, b, max_seq_len=192, n_slots=3, seed=31), f"f32 rope nh={nh} T={T} {tile}")
 
 
 @pytest.mark.parametrize("kind,M,N,K", [(S.LINEAR_SWIGLU, 1021, 13824, 1024), (S.LINEAR_SWIGLU, 544, 17920, 1024),
