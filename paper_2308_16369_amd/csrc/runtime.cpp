@@ -52,6 +52,8 @@ int hip_fail(hipError_t e, const char* what) {
 constexpr int SPLIT_KEYS = 512;   // keys per decode-attention work item
 constexpr int PRE_SPLIT = 256;    // smallest key split of a chunk-attention work item
 constexpr int QBLOCK = PREFILL_QBLOCK;   // chunk rows per chunk-attention work item (the larger size)
+constexpr double SMALL_BLOCK_TILE = 0.82;   // bf16: a 128-row block's time per key tile, a 256-row one's being 1
+constexpr double F32_TILE_US_64 = 2.46, F32_TILE_US_128 = 4.43;   // fp32 chunk block per 64-key tile, by head_dim
 constexpr int PARTS_ROWS = 512;   // split-K partials are sized for batches up to this many rows (larger
                                   // batches fill the GPU without splitting; with less room fewer splits run)
 
@@ -255,7 +257,7 @@ Plan make_plan(const sarathi_model_cfg* cfg, const BatchDesc& b) {
     const std::vector<int> sizes =
         f32 ? std::vector<int>{PREFILL_QBLOCK_F32} : std::vector<int>{QBLOCK, PREFILL_QBLOCK_SMALL};
     for (const int qbs : sizes) {
-      const double per_tile = qbs == QBLOCK ? 1.0 : 0.82;
+      const double per_tile = qbs == PREFILL_QBLOCK_SMALL ? SMALL_BLOCK_TILE : 1.0;
       std::vector<int> qt;
       int t_max = 1;
       for (const ChunkDesc& c : b.chunks)
@@ -287,14 +289,16 @@ Plan make_plan(const sarathi_model_cfg* cfg, const BatchDesc& b) {
       // A few rows of a few heads are as well taken one by one, each a block
       // (a chunk row at position p is a decode with ctx = p): row attention
       // reads ~7.2 TB/s out of L2 beside ~4 us of launch and latency; the chunk
-      // kernel takes 5 us (head_dim 64) or 9 (128) per 64-key tile of its
-      // longest block.  64 rows x 4 heads at 128: 7.7 against 16.5 us; 128 rows
-      // x 40 heads at 256: 164 (of 235 with 16 decodes) against 27.
+      // kernel's rounds take ~2.5 us (head_dim 64) or ~4.4 (128) per 64-key tile
+      // of the longest block and of its 4 tiles of fixed cost.  64 rows x 4
+      // heads (64) at 128: 7.7 us against 16.5; 128 rows x 40 heads (128) at
+      // 256: 164 (of 235 with 16 decodes) against 27.
       double bytes = 0;
       for (const ChunkDesc& c : b.chunks) bytes += c.len * (c.offset + 0.5 * (c.len + 1));
       bytes *= (double)cfg->n_heads * cfg->head_dim * 2 * 4;
       // best = rounds x (longest + 4 tiles) of the block model
-      if (bytes / 7.2e6 + 4.0 < best * (1.0 + 0.0625 * cfg->head_dim) * 0.6) p.row_base = 0;
+      const double tile_us = cfg->head_dim == 64 ? F32_TILE_US_64 : F32_TILE_US_128;
+      if (bytes / 7.2e6 + 4.0 < best * tile_us) p.row_base = 0;
     }
   }
   if (p.row_base > 0) {
