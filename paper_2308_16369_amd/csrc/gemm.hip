@@ -616,11 +616,12 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP)) void gemm_ws_kernel(GemmP p)
 }
 
 // ============================================================================ bf16 MFMA, quadrant tiles
-// Large batches (192 and 256 rows by 256 W rows per block).  At these shapes
-// the matrix cores are the bound, and the chip's power: with operands resident
-// the 256 x 256 loop runs at 97% of the matrix issue rate, at the ~1.8 GHz
-// that the power limit leaves (1400 TFLOP/s; a large library product measures
-// 1261 here).  What the smaller tiles lack is operand feed: a CU keeps ~45 KB
+// Large batches (192 and 256 rows by 256 W rows per block, 288 by 192).  With
+// operands resident the 256 x 256 loop is bound by the matrix cores and the
+// chip's power (a probe: 97% of the matrix issue rate, at the ~1.8 GHz that the
+// power limit leaves); in the layers the matrix cores are busy 44-57% of the
+// cycles, 0.9-1.3 PFLOP/s (an 8192^3 library product: 1.24-1.34 on these
+// cards).  What the smaller tiles lack is operand feed: a CU keeps ~45 KB
 // of loads in flight, ~30 bytes per clock at HBM latency, and 160 x 256 needs
 // 41 per matrix clock where 256 x 256 needs 32.
 //
@@ -1274,8 +1275,9 @@ static hipError_t run_ws_f32(int epi, int cfg, const GemmP& p, hipStream_t s) {
 // MI355X measurements of the LLaMA-13B / 33B shapes.  Each CU runs one block
 // at a time and is bound by its outstanding memory requests: a 64-wide k-tile
 // costs ~1.9 ns per A row (L2 hits) and ~3.1 ns per W row when two M-tiles
-// share the W panel (~4.2 ns when one block streams it alone: every row an
-// HBM miss); a block adds ~3 us of pipeline fill plus its output writes
+// share the W panel (~4.2 ns when one block streams it alone, every row an HBM
+// miss: taken before such loads were non-temporal, which made them 9-12%
+// faster); a block adds ~3 us of pipeline fill plus its output writes
 // (~40 GB/s per CU); blocks beyond the first 256 run as another round.  The
 // quadrant kernel's tiles have prices of their own (above).  A
 // split-K op's reduction pass reads the fp32 partials and writes the result

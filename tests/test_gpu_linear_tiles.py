@@ -1,8 +1,8 @@
 """Edges of the linear ops' matrix-core kernels through the C-ABI: the large
-bf16 tiles (192 x 256 and 256 x 256) at one to three k-tiles, rows around the
-tile height, column counts that are no multiple of four and an output that is
-not 16-byte aligned; every fp32 tile at K tails and partial tiles, split and
-unsplit.
+bf16 tiles (288 x 192, 192 x 256 and 256 x 256) at one to three k-tiles, rows
+around the tile height, column counts that are no multiple of four and an output
+that is not 16-byte aligned; their tails; the streamed instances of the others;
+every fp32 tile at K tails and partial tiles, split and unsplit.
 
 Tolerances: bf16 results are one rounding (2^-9) from an fp32 sum whose terms
 the test keeps at |x w| <= ~0.5, so 1e-2 of the largest output; fp32 sums of K
@@ -62,6 +62,64 @@ def test_quad_tile_edges(tile, mnk, shift):
             torch.cuda.synchronize()
             assert _err(out.view(M, N), _ref(kind, x, w, resid, N)) <= 1e-2, (kind, n_split)
             assert bool((buf[:shift] == 7.0).all()) and bool((buf[shift + M * N:] == 7.0).all()), (kind, n_split)
+
+
+PRODUCER_TILES = [(64, 64), (64, 128), (64, 256), (96, 128), (96, 192), (96, 256), (128, 128), (128, 192), (128, 224),
+                  (128, 256), (160, 128), (160, 192), (160, 224), (160, 256)]
+STREAMED = 32 << 20   # W of this many bytes and one M-tile: loaded non-temporally, by an instance of its own
+
+
+@pytest.mark.parametrize("tile", PRODUCER_TILES)
+def test_streamed_weights(tile):
+    """Every tile with one M-tile over 32 MB of weights, every plain epilogue, unsplit and split."""
+    index = [S.sarathi_linear_tile_shape(t) for t in range(S.sarathi_linear_tile_count())].index(tile)
+    M, K = tile[0] - 3, 1088
+    for kind in KINDS:
+        N = 7723 if kind == S.LINEAR_SWIGLU else 15437
+        w_rows = 2 * N if kind == S.LINEAR_SWIGLU else N
+        assert w_rows * K * 2 >= STREAMED
+        g = torch.Generator(device="cuda").manual_seed(M + kind)
+        x = torch.empty(M, K, device="cuda").normal_(generator=g).bfloat16()
+        w = torch.empty(w_rows, K, device="cuda").normal_(0, 0.05, generator=g).bfloat16()
+        z = x.double() @ w.double().t()
+        resid = None
+        if kind == S.LINEAR_SWIGLU:
+            z = torch.nn.functional.silu(z[:, :N]) * z[:, N:]
+        elif kind == S.LINEAR_GELU:
+            z = torch.nn.functional.gelu(z)
+        elif kind in (S.LINEAR_RESID, S.LINEAR_RESID_F32IN):
+            resid = torch.empty(M, N, device="cuda").normal_(generator=g)
+            resid = resid.bfloat16() if kind == S.LINEAR_RESID else resid
+            z += resid.double()
+        scratch = torch.empty(S.sarathi_linear_scratch_bytes(M, N), dtype=torch.uint8, device="cuda")
+        for n_split in (1, 3) if resid is not None else (1,):
+            out = torch.full((M, N), float("nan"), device="cuda",
+                             dtype=torch.float32 if kind == S.LINEAR_RESID else torch.bfloat16)
+            S.sarathi_linear_tiled(kind, M, N, K, x.data_ptr(), w.data_ptr(), 0 if resid is None else resid.data_ptr(),
+                                   out.data_ptr(), scratch.data_ptr(), scratch.numel(), index, n_split,
+                                   torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+            assert _err(out, z.cpu()) <= 1e-2, (kind, n_split)
+
+
+@pytest.mark.parametrize("H,nh,T,tile", [(1536, 29, 5, (64, 64)), (1024, 43, 5, (64, 128)), (512, 129, 5, (64, 256)),
+                                         (1024, 43, 70, (96, 128)), (512, 86, 5, (96, 192)), (512, 129, 70, (96, 256)),
+                                         (1024, 43, 100, (128, 128)), (512, 86, 100, (128, 192)),
+                                         (512, 129, 100, (128, 224)), (1024, 65, 140, (160, 128)),
+                                         (512, 86, 140, (160, 192)), (512, 129, 140, (160, 224))])
+def test_streamed_weights_rope_layer(H, nh, T, tile):
+    """The rotary + KV-append epilogue behind a streamed QKV weight."""
+    import numpy as np
+
+    import workloads as wl
+    from test_gpu_parity import run_and_check
+    assert S.sarathi_linear_plan(S.BF16, S.LINEAR_PLAIN, T, 3 * nh * 128, H, 0)[:2] == tile
+    assert T <= tile[0] and 3 * nh * 128 * H * 2 >= STREAMED
+    shape = wl.LayerShape(hidden=H, n_heads=nh, head_dim=128, ffn=max(4096, nh * 128), dtype="bf16")
+    b = wl.Batch(prefill_slot=0, chunk_offset=17, chunk_len=T - 2, decode_slots=np.array([1, 2], np.int32),
+                 decode_ctx=np.array([3, 190], np.int32))
+    run_and_check(wl.make_instance(shape, b, max_seq_len=192, n_slots=3, seed=37),
+                  f"streamed rope nh={nh} T={T} {tile}")
 
 
 @pytest.mark.parametrize("mnk", [(33, 65, 40), (97, 129, 104), (161, 1100, 72), (8, 33, 2048), (1030, 260, 136)])

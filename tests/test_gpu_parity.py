@@ -167,7 +167,7 @@ def test_linear_split_k_deterministic(kind):
 @pytest.mark.parametrize("kind", [S.LINEAR_RESID, S.LINEAR_RESID_F32IN])
 @pytest.mark.parametrize("mnk", [(72, 256, 688), (5, 17, 1000), (130, 200, 4104)])
 def test_linear_split_k_fp32(kind, mnk):
-    """fp32 residual ops split over K when their 64x64 tiles leave most CUs
+    """fp32 residual ops split over K when their tiles leave most CUs
     idle (ragged last split included): bit-identical run to run, and both
     the split and the unsplit op (no scratch) within the fp32 tolerance."""
     M, N, K = mnk
